@@ -667,12 +667,11 @@ int kvr_capacity_replay(const double *d_arrival_s, const double *d_wait_s,
     if ((rc = check_workspace(d_ws, *ws_bytes, need)) != KVR_OK) return rc;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     int *status = static_cast<int *>(d_ws);
-    KVR_TRY(kvr::launch_clear_status(status, s));
     KVR_MARK(g_prof_begin, s);
     KVR_TRY(kvr::launch_replay(d_arrival_s, d_wait_s, d_ctx_tokens, n_reps, n, t2, n_t2,
                                (int64_t)c2d, p->b2_per_token, p->b3_per_token,
                                at<char>(d_ws, kStatusBytes), d_cost, d_restored_tokens,
-                               d_admitted, status, s));
+                               d_admitted, 0.0, nullptr, status, s));
     KVR_MARK(g_prof_end, s);
     return KVR_OK;
 }
@@ -708,14 +707,11 @@ int kvr_controller_select(const double *d_arrival_s, const double *d_wait_s,
     int *status = static_cast<int *>(d_ws);
     int64_t *rest = at<int64_t>(d_ws, off_rest), *adm = at<int64_t>(d_ws, off_adm);
     const double timers[2] = {t2, std::numeric_limits<double>::infinity()};
-    KVR_TRY(kvr::launch_clear_status(status, s));
     KVR_MARK(g_prof_begin, s);
     KVR_TRY(kvr::launch_replay(d_arrival_s, d_wait_s, d_ctx_tokens, reps, n, timers, 2,
                                (int64_t)c2d, p->b2_per_token, p->b3_per_token,
                                at<char>(d_ws, off_replay), at<double>(d_ws, off_cost), rest, adm,
-                               status, s));
-    KVR_TRY(kvr::launch_short_count(d_wait_s, d_ctx_tokens, reps * n, t_star,
-                                    at<char>(d_ws, off_cnt), status, s));
+                               t_star, at<char>(d_ws, off_cnt), status, s));
     KVR_TRY(kvr::launch_controller_final(rest, adm, reps, reps * n, at<char>(d_ws, off_cnt), t2,
                                          t_star, p->b2_per_token, p->b3_per_token, d_out, s));
     KVR_MARK(g_prof_end, s);

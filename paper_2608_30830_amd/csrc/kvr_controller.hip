@@ -2,8 +2,9 @@
 // statistic of Section 4.3 / Figure 4(d).
 //
 // The two host branches are replayed by the admission-replay kernels (one
-// lane per (sequence, branch)); what remains is integer bookkeeping: the
-// share of waits at or below t* = beta_3 / alpha_1, the token total, and the
+// wave per (sequence, branch)), whose first pass over the rows also counts the
+// waits at or below t* = beta_3 / alpha_1 and the tokens (a pass of its own
+// only for kvr_crossover_statistic); what remains is integer bookkeeping: the
 // per-branch sums of restored tokens and admissions.  All of it is exact
 // integer arithmetic, so atomics and reduction order cannot change a result;
 // the two totals b2*R + b3*(Ttot - R) are formed once, without contraction.

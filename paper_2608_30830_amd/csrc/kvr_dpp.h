@@ -67,6 +67,20 @@ __device__ __forceinline__ V wave_incl_scan(V x)
     return x;
 }
 
+// Inclusive maximum over the 64 lanes of a wave, by the same moves.
+__device__ __forceinline__ int32_t wave_incl_max(int32_t x)
+{
+    constexpr uint64_t kNone = 0x80000000u;   // the smallest value: a lane without a source
+    auto up = [](int32_t a, int32_t b) { return a > b ? a : b; };
+    x = up(x, dpp_move<kDppRowShr1, 0xf>(x, kNone));
+    x = up(x, dpp_move<kDppRowShr2, 0xf>(x, kNone));
+    x = up(x, dpp_move<kDppRowShr4, 0xf>(x, kNone));
+    x = up(x, dpp_move<kDppRowShr8, 0xf>(x, kNone));
+    x = up(x, dpp_move<kDppRowBcast15, 0xa>(x, kNone));
+    x = up(x, dpp_move<kDppRowBcast31, 0xc>(x, kNone));
+    return x;
+}
+
 // Sum over the 64 lanes in wave_incl_scan's tree, returned to every lane
 // (lane 63's inclusive value, read as a scalar).
 template <typename V>

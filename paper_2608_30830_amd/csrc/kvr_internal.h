@@ -133,12 +133,15 @@ hipError_t launch_select(const double *cost, int64_t batch, int L, int64_t P, in
                          int last_inf, int32_t *best, double *best_cost, int32_t *branch,
                          hipStream_t stream);
 
-// Finite-capacity admission replay (n <= kReplayMaxN requests per sequence).
+// Finite-capacity admission replay (n <= kReplayMaxN requests per sequence);
+// clears the status word first.  With counts (count_ws_bytes() bytes, cleared
+// here) the waits <= t_star and the token total are counted too.
 size_t replay_ws_bytes(int64_t reps, int64_t n, int K);
 hipError_t launch_replay(const double *arrival, const double *wait, const int32_t *ctx,
                          int64_t reps, int64_t n, const double *h_t2, int K, int64_t c2, double b2,
                          double b3, void *ws, double *cost, int64_t *restored,
-                         int64_t *admitted, int *status, hipStream_t stream);
+                         int64_t *admitted, double t_star, void *counts, int *status,
+                         hipStream_t stream);
 
 // Controller tail: share of waits <= t_star and token total over N waits,
 // then the branch totals from the replay's per-row counts [reps][2].

@@ -135,3 +135,35 @@ def test_replay_forty_lane_waves(kvr, oracle_mod, reps, n, n_timers):
     assert np.all(np.abs(cost[rows] - oc) <= 4 * np.spacing(oc))
     assert np.all((adm >= np.minimum(n, 425)) & (adm <= n))
     assert np.all(rest <= adm)
+
+
+def _odd_rows(shape, n, rng):
+    """Arrivals and waits of rows whose time buckets or same-wave releases are extreme."""
+    w = rng.exponential(40.0, n)
+    if shape == "one_instant":
+        arr = np.full(n, 3.5)
+    elif shape == "two_bursts":          # all arrivals in two of the time buckets
+        arr = np.where(np.arange(n) < n // 2, 1.0, 1.0e9)
+    elif shape == "denormal_span":       # the bucket width underflows
+        arr = np.minimum(np.arange(n), 3) * 5e-324
+    elif shape == "huge":                # departures overflow to infinity
+        arr = np.linspace(0.0, 1.7e308, n)
+        w = np.where(rng.random(n) < 0.5, 1.0e308, w)
+    elif shape == "chains":              # every request released at one of the next few arrivals
+        arr = np.arange(n) * 1.0
+        w = rng.integers(0, 4, n) * 1.0
+    else:                                # "ragged": gaps over nine orders of magnitude
+        arr = np.cumsum(10.0 ** rng.uniform(-6.0, 3.0, n))
+    return arr, w
+
+
+@pytest.mark.parametrize("shape", ["one_instant", "two_bursts", "denormal_span", "huge", "chains",
+                                   "ragged"])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 1024, 1025, 4096, 4097])
+def test_replay_odd_rows(kvr, oracle_mod, shape, n):
+    rng = np.random.Generator(np.random.PCG64(n))
+    rows = [_odd_rows(shape, n, rng) for _ in range(2)]
+    arr, w = np.stack([r[0] for r in rows]), np.stack([r[1] for r in rows])
+    T = rng.integers(1, 50, (2, n)).astype(np.int32)
+    for c2 in (1, 5, 64, n + 7):
+        _check(kvr, oracle_mod, arr, w, [2.0, 33.0, math.inf], c2, T)
