@@ -296,20 +296,9 @@ def time_paths(kvr, workloads, torch):
     return res
 
 
-# Algorithmic bytes per key of the SORTED path (no order requested): the first
-# digit's tile histograms from the waits (8 B read); the histograms of the
-# other seven digits (below 2^22 keys each reads the 8-byte keys; from 2^22 the
-# one-byte digits that the previous scatter wrote: 1 B read, and 1 B written
-# by each of the first seven scatters); eight scatters (12 B read, 12 B
-# written each; the first reads the waits and context sizes); the tile and
-# 64-key chunk sums (12 B read, 16 B written per 64 keys).  The closed form
-# then reads N and S at its query positions only.
-SORT_DIGIT_BYTES_FROM = 1 << 22
-
-
-def sort_bytes_per_key(n: int) -> float:
-    hist = 7 * (1 + 1) if n >= SORT_DIGIT_BYTES_FROM else 7 * 8
-    return 8 + hist + 8 * 24 + 12 + 16 / 64
+# Bytes per wait of the SORTED path without a requested order: each wait and
+# context size read once.
+SORTED_BYTES_PER_WAIT = 12
 
 
 def time_factored(kvr, workloads, torch):
@@ -335,7 +324,8 @@ def time_factored(kvr, workloads, torch):
 
 def time_sort_scale(kvr, workloads, torch):
     """Median milliseconds per SORTED kvr_cost_grid call at 2^20, 2^22, 2^23
-    and 2^24 waits and the algorithmic bytes per second that implies."""
+    and 2^24 waits, without a requested order (and the bytes per second that
+    reading the sample once implies) and with it."""
     res = {}
     for lg in (20, 22, 23, 24):
         wl = workloads.sort_scale_case(lg)
@@ -348,10 +338,13 @@ def time_sort_scale(kvr, workloads, torch):
         T = torch.as_tensor(wl.ctx_tokens).cuda()
         call = kvr.CostGridCall(w, T, pr, g, method=kvr.KVR_SORTED)
         ms = _median_ms(torch, call.launch, 11)
-        bps = sort_bytes_per_key(wl.n) * wl.n / (ms * 1e-3)
-        res[wl.name] = {"ms": ms, "keys_per_s": wl.n / (ms * 1e-3), "algorithmic_bytes_per_s": bps,
-                        "hbm_frac": bps / (HBM_PEAK_TBS * 1e12)}
-        log(f"[bench] sorted {wl.name}: {ms:.3f} ms, {bps / 1e12:.2f} TB/s algorithmic")
+        bps = SORTED_BYTES_PER_WAIT * wl.n / (ms * 1e-3)
+        order = kvr.CostGridCall(w, T, pr, g, method=kvr.KVR_SORTED, want_perm=True)
+        oms = _median_ms(torch, order.launch, 11)
+        res[wl.name] = {"ms": ms, "waits_per_s": wl.n / (ms * 1e-3), "algorithmic_bytes_per_s": bps,
+                        "hbm_frac": bps / (HBM_PEAK_TBS * 1e12), "with_order_ms": oms}
+        log(f"[bench] sorted {wl.name}: {ms:.3f} ms, {bps / 1e12:.2f} TB/s algorithmic; "
+            f"with the order {oms:.3f} ms")
     return res
 
 

@@ -387,6 +387,7 @@ int kvr::cost_grid_entry(const double *d_wait_s, const int32_t *d_ctx_tokens, in
     bool small = false;
     size_t off_t1 = kStatusBytes, off_t2 = 0, off_a2 = 0, off_sort = 0;
     int32_t Lpad = g->n_lam;
+    const int64_t P = (int64_t)g->n_t1 * g->n_t2;
     if (method == KVR_BRUTE) {
         bp = plan_brute(1, n, n, *g, false, true);
         small = small_plan_applies(bp, *g, n);
@@ -412,7 +413,10 @@ int kvr::cost_grid_entry(const double *d_wait_s, const int32_t *d_ctx_tokens, in
         off_t2 = off_t1 + align256(sizeof(double) * g->n_t1);
         off_a2 = off_t2 + align256(sizeof(double) * g->n_t2);
         off_sort = off_a2 + align256(sizeof(double) * Lpad);
-        need = off_sort + kvr::sort_ws_bytes(n);
+        // the same workspace with and without a requested order
+        need = kvr::sort_ws_bytes(n);
+        if (kvr::bins_apply(P)) need = std::max(need, kvr::bin_ws_bytes(g->n_t1, P));
+        need += off_sort;
     }
     if (d_ws == nullptr) {
         *ws_bytes = need;
@@ -466,9 +470,16 @@ int kvr::cost_grid_entry(const double *d_wait_s, const int32_t *d_ctx_tokens, in
         return KVR_OK;
     }
     if ((rc = stage_tables(d_ws, off_t1, off_t2, off_a2, Lpad, *p, *g, s, tb)) != KVR_OK) return rc;
+    KVR_MARK(g_prof_begin, s);
+    if (d_perm == nullptr && kvr::bins_apply(P)) {
+        kvr::BinWs bws{};
+        kvr::bin_ws_carve(at<char>(d_ws, off_sort), n, g->n_t1, P, bws);
+        KVR_TRY(kvr::launch_binned(d_wait_s, d_ctx_tokens, n, tb, pr, bws, d_cost, status, s));
+        KVR_MARK(g_prof_end, s);
+        return KVR_OK;
+    }
     kvr::SortWs sws{};
     kvr::sort_ws_carve(at<char>(d_ws, off_sort), n, sws);
-    KVR_MARK(g_prof_begin, s);
     KVR_TRY(kvr::launch_sorted_path(d_wait_s, d_ctx_tokens, n, tb, pr, sws, d_cost, d_perm, status, s));
     KVR_MARK(g_prof_end, s);
     return KVR_OK;

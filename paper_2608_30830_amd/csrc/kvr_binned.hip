@@ -1,0 +1,397 @@
+// SORTED cost grid of one sample when no order is requested: N and S by
+// deadline bins instead of a sort.
+//
+// The closed form (kvr_device.h, closed_form_values) needs N(x) = sum T [w <= x]
+// and S(x) = sum T w [w <= x] only at the grid's own thresholds x: the K1
+// timers t1 and the K1*K2 deadlines fl(t1 + t2).  With the thresholds in order,
+// thr[0] <= thr[1] <= ..., and bin(x) = the number of thresholds strictly below
+// x, w <= x holds exactly when bin(w) <= bin(x); so N and S at a threshold are
+// inclusive prefix sums over its bin of per-bin sums, and the sample is read
+// once (12 B per wait) instead of passing eight times through a radix sort
+// (about 226 B per wait).
+//
+// The per-bin sums are exact integers, so neither the order of the atomics nor
+// the split of the sample over blocks can change a result.  Within bin b the
+// waits lie in (lower edge, upper edge], so T*w = T*edge + T*(w - edge), and
+// w - edge is kept as a 64-bit fraction of the power of two above the bin's
+// width; T times it (95 bits) is added in two 48-bit limbs.  So that this
+// fraction is at least as fine as the binary64 product T*w for any grid and any
+// wait, the powers 2^(10 q) over the whole range of finite numbers (and the
+// largest one) are thresholds too: no bin is wider than 2^10 times its lower
+// edge, and every wait has an upper edge.
+//
+// Measured on MI355X, the whole call against the sort: 2^24 waits and 66
+// thresholds 95 us against 1,092 (the sums 87 us, 2.3 TB/s); 100,003 waits and
+// 510 thresholds 31 us against 104 (28 launches of 3-5 us each, four now).
+#include "kvr_device.h"
+#include "kvr_dpp.h"
+
+namespace kvr {
+
+constexpr int kBinThreads = 1024;
+constexpr int kBinIlp = 4;                 // waits per thread in flight
+constexpr int kBinRange = 4095;            // bins of one range: 128 KiB of LDS with their edges
+constexpr int64_t kBinChunk = 65536;       // waits per block at most: 48-bit limbs, 64-bit sums
+constexpr int64_t kBinBlocks = 512;        // blocks that fill the chip (two to a CU)
+constexpr int kBinFused = 4096;            // bins that the closed form's own blocks scan
+constexpr int kBinWords = 4;               // per bin: sum of T, then three 32-bit limbs of S
+constexpr int kFixedEdges = 211;           // 2^-1070, 2^-1060, ..., 2^1020, the largest finite
+constexpr int kBinLdsTable = 4096;         // timer-table entries staged in LDS
+constexpr int kItemLanes = 8;              // lanes per threshold
+constexpr int kFormPolicies = 64;          // policies of one closed-form block
+
+static inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// Waits per block: about one block per CU before a thread takes a second wait,
+// two blocks per CU for large samples, never more than kBinChunk.
+static int64_t bin_chunk(int64_t n)
+{
+    int64_t per = cdiv(n, kBinThreads * (kBinBlocks / 2));
+    if (per > 4) per = cdiv(n, kBinThreads * kBinBlocks);
+    const int64_t c = per * kBinThreads;
+    return c < kBinChunk ? c : kBinChunk;
+}
+
+// Policies up to which the bins replace the sort: nine ranges of bins at most,
+// each of which reads the sample once.
+bool bins_apply(int64_t P) { return P <= 16384; }
+
+size_t bin_ws_bytes(int64_t K1, int64_t P)
+{
+    const int64_t M = K1 + P + kFixedEdges;
+    return align256(sizeof(double) * (M + 1)) + align256(sizeof(int32_t) * (K1 + P)) +
+           align256(sizeof(uint64_t) * kBinWords * (M + 1)) +
+           2 * align256(sizeof(double) * (M + 1));
+}
+
+void bin_ws_carve(void *base, int64_t n, int64_t K1, int64_t P, BinWs &ws)
+{
+    char *p = static_cast<char *>(base);
+    auto take = [&](size_t bytes) {
+        char *q = p;
+        p += align256(bytes);
+        return q;
+    };
+    ws.M = (int)(K1 + P) + kFixedEdges;
+    ws.chunk = bin_chunk(n);
+    ws.nblocks = (int)cdiv(n, ws.chunk);
+    ws.thr = (double *)take(sizeof(double) * (ws.M + 1));
+    ws.at = (int32_t *)take(sizeof(int32_t) * (K1 + P));
+    ws.bins = (unsigned long long *)take(sizeof(uint64_t) * kBinWords * (ws.M + 1));
+    ws.cumN = (int64_t *)take(sizeof(int64_t) * (ws.M + 1));
+    ws.cumS = (double *)take(sizeof(double) * (ws.M + 1));
+}
+
+__device__ __forceinline__ double fixed_edge(int q)
+{
+    if (q == kFixedEdges - 1) return 1.7976931348623157e308;
+    const int ex = 10 * q - 1070;
+    const uint64_t bits = ex >= -1022 ? (uint64_t)(ex + 1023) << 52 : 1ull << (ex + 1074);
+    return __longlong_as_double((long long)bits);
+}
+
+// Item i < K1 is timer t1[i], item K1 + f policy f's deadline, the rest the
+// fixed edges.  The bin of a timer or a deadline (the thresholds strictly
+// below it) goes to at[i]; the thresholds in order to
+// thr[0..M) (an item equal to others fills their whole run, and is left out
+// when its neighbour on the searched axis is equal, so a run has at most
+// min(K1, K2) + 2 writers, all of one value), thr[M] = inf.  The bins are
+// cleared.  kItemLanes lanes share an item's searches.
+__global__ void __launch_bounds__(256) bin_thresholds_kernel(Tables tb, BinWs ws)
+{
+    __shared__ double lt[kBinLdsTable];
+    const double *t1v = tb.t1, *t2v = tb.t2;
+    if (tb.K1 + tb.K2 <= kBinLdsTable) {   // uniform
+        for (int q = threadIdx.x; q < tb.K1 + tb.K2; q += blockDim.x)
+            lt[q] = q < tb.K1 ? tb.t1[q] : tb.t2[q - tb.K1];
+        __syncthreads();
+        t1v = lt;
+        t2v = lt + tb.K1;
+    }
+    const int lane = (int)threadIdx.x % kItemLanes;
+    const int i = (int)(blockIdx.x * (blockDim.x / kItemLanes) + threadIdx.x / kItemLanes);
+    if (i > ws.M) return;   // whole groups of lanes
+    if (lane < kBinWords) ws.bins[(int64_t)i * kBinWords + lane] = 0ull;
+    if (i == ws.M) {
+        if (lane == 0) ws.thr[i] = INFINITY;
+        return;
+    }
+    double x;
+    bool fill = true;
+    const int items = ws.M - kFixedEdges;
+    if (i < tb.K1) {
+        x = t1v[i];
+    } else if (i >= items) {
+        x = fixed_edge(i - items);
+    } else {
+        const int f = i - tb.K1, a = f / tb.K2, k = f % tb.K2;
+        x = t1v[a] + t2v[k];
+        if (tb.K1 <= tb.K2) fill = k == 0 || t1v[a] + t2v[k - 1] != x;
+        else fill = a == 0 || t1v[a - 1] + t2v[k] != x;
+    }
+    int below = 0, equal = 0;   // this lane's rows (or columns), then all of them
+    deadlines_rank(t1v, tb.K1, t2v, tb.K2, x, lane, kItemLanes, below, equal);
+    if (lane == 0) {            // the timers are distinct: at most one equals x
+        const int q = rank_below(t1v, tb.K1, 0.0, x);
+        below += q;
+        if (q < tb.K1 && t1v[q] == x) ++equal;
+    }
+    if (lane == 1) {
+        int lo = 0, hi = kFixedEdges;   // first fixed edge >= x
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (fixed_edge(mid) < x) lo = mid + 1;
+            else hi = mid;
+        }
+        below += lo;
+        if (lo < kFixedEdges && fixed_edge(lo) == x) ++equal;
+    }
+    for (int off = kItemLanes / 2; off > 0; off >>= 1) {
+        below += __shfl_xor(below, off, kItemLanes);
+        equal += __shfl_xor(equal, off, kItemLanes);
+    }
+    if (lane == 0 && i < items) ws.at[i] = below;
+    if (fill)
+        for (int q = below + lane; q < below + equal; q += kItemLanes) ws.thr[q] = x;
+}
+
+// Block (range, chunk): the chunk's waits whose bin lies in the range
+// [b0, b0 + nb) are added to the range's bins in LDS, then to the global ones.
+// RP is the power of two above the number of bins (kBinRange + 1 at most): edge[0]
+// is the range's lower edge, edge[1 + i] the upper edge of bin b0 + i, and
+// from edge[1 + nb] on infinity, so that the search needs no bounds.
+template <int RP>
+__global__ void __launch_bounds__(kBinThreads) bin_sums_kernel(const double *__restrict__ w,
+                                                               const int32_t *__restrict__ T,
+                                                               int64_t n, BinWs ws, int nranges,
+                                                               int *status)
+{
+    __shared__ double edge[RP + 1];
+    __shared__ unsigned long long sumT[RP], lo48[RP], hi48[RP];
+    const int range = (int)(blockIdx.x % nranges);
+    const int64_t chunk = blockIdx.x / nranges;
+    const int b0 = range * kBinRange;
+    const int total = ws.M + 1;                       // bins 0..M
+    const int nb = total - b0 < kBinRange ? total - b0 : kBinRange;
+    for (int q = threadIdx.x; q < RP; q += kBinThreads) {
+        edge[q + 1] = q < nb ? ws.thr[b0 + q] : INFINITY;
+        sumT[q] = lo48[q] = hi48[q] = 0ull;
+    }
+    // below the first range lies nothing: waits are >= 0, so an edge of -1
+    // keeps w = 0 inside bin 0, whose offsets are taken from 0
+    if (threadIdx.x == 0) edge[0] = b0 > 0 ? ws.thr[b0 - 1] : -1.0;
+    __syncthreads();
+    const double lower = edge[0], upper = edge[nb];   // of the whole range
+    const int64_t j0 = chunk * ws.chunk;
+    const int64_t j1 = j0 + ws.chunk < n ? j0 + ws.chunk : n;
+    bool bad = false;
+    for (int64_t jb = j0 + threadIdx.x; jb < j1; jb += kBinIlp * kBinThreads) {
+        double x[kBinIlp];
+        int32_t t[kBinIlp];
+        int pos[kBinIlp];
+#pragma unroll
+        for (int u = 0; u < kBinIlp; ++u) {   // every load in flight before the searches
+            const int64_t j = jb + u * kBinThreads;
+            const int64_t jc = j < j1 ? j : j1 - 1;
+            x[u] = w[jc];
+            t[u] = T[jc];
+        }
+#pragma unroll
+        for (int u = 0; u < kBinIlp; ++u) {
+            const uint64_t bits = (uint64_t)__double_as_longlong(x[u]);
+            if (!(bits < 0x7ff0000000000000ull || bits == 0x8000000000000000ull)) {
+                bad = true;
+                x[u] = 0.0;
+            }
+            if (t[u] < 1) {
+                bad = true;
+                t[u] = 1;
+            }
+            pos[u] = 0;
+        }
+#pragma unroll
+        for (int step = RP / 2; step > 0; step >>= 1) {   // edges of the range below x
+#pragma unroll
+            for (int u = 0; u < kBinIlp; ++u)
+                if (edge[pos[u] + step] < x[u]) pos[u] += step;
+        }
+#pragma unroll
+        for (int u = 0; u < kBinIlp; ++u) {
+            if (jb + u * kBinThreads >= j1 || !(x[u] > lower && x[u] <= upper)) continue;
+            const double top = edge[pos[u] + 1];
+            atomicAdd(&sumT[pos[u]], (unsigned long long)t[u]);
+            double base = edge[pos[u]];
+            base = base > 0.0 ? base : 0.0;
+            // width < 2^(e - 1022): (w - base) * 2^(32 - (e - 1022)) < 2^32.
+            // (A width below 2^-958 takes the scale of 2^-958.)
+            const uint32_t e = (uint32_t)((uint64_t)__double_as_longlong(top - base) >> 52);
+            const uint32_t es = e > 64u ? e : 64u;
+            const double d = (x[u] - base) *
+                             __longlong_as_double((long long)((uint64_t)(2077u - es) << 52));
+            const uint32_t dh = (uint32_t)d;
+            const uint32_t dl = (uint32_t)((d - (double)dh) * 4294967296.0);
+            const uint64_t p0 = (uint64_t)(uint32_t)t[u] * dl;
+            const uint64_t p1 = (uint64_t)(uint32_t)t[u] * dh + (p0 >> 32);
+            atomicAdd(&lo48[pos[u]], (unsigned long long)(((p1 & 0xffffu) << 32) | (uint32_t)p0));
+            atomicAdd(&hi48[pos[u]], (unsigned long long)(p1 >> 16));
+        }
+    }
+    if (bad) flag_domain(status);
+    __syncthreads();
+    for (int q = threadIdx.x; q < nb; q += kBinThreads) {
+        if (sumT[q] == 0ull) continue;
+        unsigned long long *out = ws.bins + (int64_t)(b0 + q) * kBinWords;
+        atomicAdd(out, sumT[q]);
+        const uint64_t lo = lo48[q], hi = hi48[q];
+        // hi * 2^48 + lo as three 32-bit limbs (the last with the carries)
+        const uint64_t l1 = (lo >> 32) + ((hi & 0xffffu) << 16);
+        if (lo | hi) {
+            atomicAdd(out + 1, (unsigned long long)(uint32_t)lo);
+            atomicAdd(out + 2, (unsigned long long)(uint32_t)l1);
+            atomicAdd(out + 3, (unsigned long long)((hi >> 16) + (l1 >> 32)));
+        }
+    }
+}
+
+// One block of kBinThreads: the inclusive prefix sums of T and T*w over the
+// bins, each thread a run of consecutive bins, in a fixed order.  An empty
+// bin's S is that of the last bin before it that is not empty, bit for bit, so
+// policies that no wait separates get equal costs.
+template <typename NOut, typename SOut>
+__device__ __forceinline__ void bin_prefix(const BinWs &ws, NOut *cumN, SOut *cumS)
+{
+    __shared__ int64_t wn[kBinThreads / kWave];
+    __shared__ double wsum[kBinThreads / kWave];
+    __shared__ int wl[kBinThreads / kWave];
+    const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
+    const int total = ws.M + 1;
+    const int per = (total + kBinThreads - 1) / kBinThreads;
+    const int q0 = t * per, q1 = q0 + per < total ? q0 + per : total;
+    auto bin_of = [&](int b, int64_t &N, double &S) {
+        const unsigned long long *in = ws.bins + (int64_t)b * kBinWords;
+        N = (int64_t)in[0];
+        const double base = b > 0 ? ws.thr[b - 1] : 0.0, top = ws.thr[b];
+        if (isinf(top)) {   // no finite wait lies beyond the last fixed edge
+            S = 0.0;
+            return;
+        }
+        const uint32_t e = (uint32_t)((uint64_t)__double_as_longlong(top - base) >> 52);
+        const int es = (int)(e > 64u ? e : 64u);
+        // the limbs count units of 2^(es - 1022 - 64)
+        const double frac = ((double)in[3] * 4294967296.0 + (double)in[2]) +
+                            (double)in[1] * 2.3283064365386963e-10;
+        S = fma(base, (double)N, ldexp(frac, es - 1022 - 32));
+    };
+    int64_t sn = 0;
+    double ss = 0.0;
+    int last = -1;
+    for (int b = q0; b < q1; ++b) {
+        int64_t N;
+        double S;
+        bin_of(b, N, S);
+        sn += N;
+        ss += S;
+        if (N != 0) last = b;
+    }
+    const int64_t xn = wave_incl_scan(sn);
+    const double xs = wave_incl_scan(ss);
+    const int xl = wave_incl_max(last);
+    if (lane == kWave - 1) {
+        wn[wave] = xn;
+        wsum[wave] = xs;
+        wl[wave] = xl;
+    }
+    __syncthreads();
+    int64_t pn = 0;
+    double ps = 0.0;
+    int pl = -1;
+    for (int q = 0; q < wave; ++q) {
+        pn += wn[q];
+        ps += wsum[q];
+        pl = wl[q] > pl ? wl[q] : pl;
+    }
+    pn += wave_lane_back(xn);
+    ps += wave_lane_back(xs);
+    const int back = __shfl_up(xl, 1, kWave);   // every lane takes part
+    if (lane > 0 && back > pl) pl = back;
+    for (int b = q0; b < q1; ++b) {
+        int64_t N;
+        double S;
+        bin_of(b, N, S);
+        pn += N;
+        ps += S;
+        cumN[b] = pn;
+        if (N != 0) cumS[b] = ps;
+    }
+    __syncthreads();
+    for (int b = q0; b < q1; ++b) {   // the empty bins
+        const bool full = cumN[b] != (b > 0 ? cumN[b - 1] : 0);
+        if (full) pl = b;
+        else cumS[b] = pl >= 0 ? cumS[pl] : 0.0;
+    }
+    __syncthreads();
+}
+
+__global__ void __launch_bounds__(kBinThreads) bin_prefix_kernel(BinWs ws)
+{
+    bin_prefix(ws, ws.cumN, ws.cumS);
+}
+
+// kFormPolicies policies per block, the block's other threads sharing their
+// loads.  FUSED: the block forms the prefix sums itself, in LDS.
+template <bool FUSED>
+__global__ void __launch_bounds__(kBinThreads) bin_form_kernel(BinWs ws, int64_t n, Tables tb,
+                                                               PriceDev pr,
+                                                               double *__restrict__ cost)
+{
+    __shared__ int64_t lN[FUSED ? kBinFused : 1];
+    __shared__ double lS[FUSED ? kBinFused : 1];
+    const int64_t *cumN = ws.cumN;
+    const double *cumS = ws.cumS;
+    if (FUSED) {
+        bin_prefix(ws, lN, lS);
+        cumN = lN;
+        cumS = lS;
+    }
+    const int64_t P = (int64_t)tb.K1 * tb.K2;
+    const int64_t f = (int64_t)blockIdx.x * kFormPolicies + threadIdx.x % kFormPolicies;
+    if (f >= P) return;
+    const int a = (int)(f / tb.K2), k = (int)(f % tb.K2);
+    const double t1 = tb.t1[a];
+    const int u1 = ws.at[a], ue = ws.at[tb.K1 + f];
+    closed_form_values(cumN[ws.M], cumN[u1], cumN[ue], cumS[u1], cumS[ue], n, tb, pr, f, t1,
+                       t1 + tb.t2[k], (int)threadIdx.x / kFormPolicies,
+                       kBinThreads / kFormPolicies, cost);
+}
+
+hipError_t launch_binned(const double *w, const int32_t *T, int64_t n, const Tables &tb,
+                         const PriceDev &pr, const BinWs &ws, double *cost_out, int *status,
+                         hipStream_t stream)
+{
+    const int64_t P = (int64_t)tb.K1 * tb.K2;
+    const int total = ws.M + 1;
+    const int nranges = (int)cdiv(total, kBinRange);
+    hipLaunchKernelGGL(bin_thresholds_kernel, dim3((unsigned)cdiv(total, 256 / kItemLanes)),
+                       dim3(256), 0, stream, tb, ws);
+    const dim3 grid((unsigned)(ws.nblocks * nranges)), block(kBinThreads);
+    if (total < 128)
+        hipLaunchKernelGGL(bin_sums_kernel<128>, grid, block, 0, stream, w, T, n, ws, nranges, status);
+    else if (total < 512)
+        hipLaunchKernelGGL(bin_sums_kernel<512>, grid, block, 0, stream, w, T, n, ws, nranges, status);
+    else if (total < 2048)
+        hipLaunchKernelGGL(bin_sums_kernel<2048>, grid, block, 0, stream, w, T, n, ws, nranges, status);
+    else
+        hipLaunchKernelGGL(bin_sums_kernel<kBinRange + 1>, grid, block, 0, stream, w, T, n, ws,
+                           nranges, status);
+    const dim3 form((unsigned)cdiv(P, kFormPolicies));
+    if (total <= kBinFused) {
+        hipLaunchKernelGGL(bin_form_kernel<true>, form, block, 0, stream, ws, n, tb, pr, cost_out);
+    } else {
+        hipLaunchKernelGGL(bin_prefix_kernel, dim3(1), block, 0, stream, ws);
+        hipLaunchKernelGGL(bin_form_kernel<false>, form, block, 0, stream, ws, n, tb, pr, cost_out);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace kvr

@@ -81,4 +81,61 @@ __device__ __forceinline__ int64_t xcd_logical_block(int64_t hw, int64_t nblocks
     return x * q + (x < rem ? x : rem) + hw / nx;
 }
 
+// Values v0 + v[q] strictly below x, for ascending v[0..K).
+__device__ __forceinline__ int rank_below(const double *v, int K, double v0, double x)
+{
+    int lo = 0, hi = K;   // first q with v0 + v[q] >= x
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (v0 + v[mid] < x) lo = mid + 1;
+        else hi = mid;
+    }
+    return lo;
+}
+
+// Grid deadlines fl(t1[a] + t2[k]) strictly below x and equal to x, added to
+// below and equal: one search along each row (column when K1 > K2, whichever
+// are fewer; rounding is monotone, so both are non-decreasing) first,
+// first + step, ...
+__device__ __forceinline__ void deadlines_rank(const double *t1v, int K1, const double *t2v, int K2,
+                                               double x, int first, int step, int &below,
+                                               int &equal)
+{
+    const bool rows = K1 <= K2;
+    const int lines = rows ? K1 : K2, len = rows ? K2 : K1;
+    const double *line0 = rows ? t1v : t2v, *v = rows ? t2v : t1v;
+    for (int q = first; q < lines; q += step) {
+        const double v0 = line0[q];
+        const int lo = rank_below(v, len, v0, x);
+        below += lo;
+        int run = lo, hi = len;   // values equal to x: [lo, run)
+        if (lo < len && v0 + v[lo] == x) {
+            while (run < hi) {
+                const int mid = (run + hi) >> 1;
+                if (v0 + v[mid] <= x) run = mid + 1;
+                else hi = mid;
+            }
+        }
+        equal += run - lo;
+    }
+}
+
+// The closed form of policy f for every load, from the tokens (N) and
+// tokens x waits (S) of the waits <= t1 and <= e; loads l0, l0 + lstep, ... are
+// written.
+__device__ __forceinline__ void closed_form_values(int64_t tot, int64_t n1, int64_t ne, double s1,
+                                                   double se, int64_t n, const Tables &tb,
+                                                   const PriceDev &pr, int64_t f, double t1,
+                                                   double e, int l0, int lstep,
+                                                   double *__restrict__ cost)
+{
+    const int64_t P = (int64_t)tb.K1 * tb.K2;
+    const double hbm = s1 + t1 * (double)(tot - n1);
+    double hold = (se - s1) - t1 * (double)(ne - n1);
+    if (!isinf(e)) hold += (e - t1) * (double)(tot - ne);
+    const double fixed = pr.a1 * hbm + pr.b2 * (double)(ne - n1) + pr.b3 * (double)(tot - ne);
+    const double nd = (double)n;
+    for (int l = l0; l < tb.L; l += lstep) cost[(int64_t)l * P + f] = (fixed + tb.a2[l] * hold) / nd;
+}
+
 }  // namespace kvr

@@ -176,14 +176,33 @@ hipError_t launch_small(const SampleSrc &src, const Tables &tb, const PriceDev &
                         const GridPlan &plan, const SmallWs &ws, double *cost_out, int *status,
                         hipStream_t stream);
 
+// SORTED without a requested order (kvr_binned.hip).
+struct BinWs {
+    double *thr;                // [M + 1] the grid's t1 timers and deadlines and the fixed edges in
+                                // order, then inf
+    int32_t *at;                // [K1 + P] thresholds strictly below each timer, then each deadline
+    unsigned long long *bins;   // [M + 1][4] sums over the waits of each bin
+    int64_t *cumN;              // [M + 1] prefix sums over the bins (grids of many policies)
+    double *cumS;
+    int M;                      // thresholds
+    int nblocks;                // chunks of the sample
+    int64_t chunk;              // waits per chunk
+};
+
+size_t bin_ws_bytes(int64_t K1, int64_t P);
+void bin_ws_carve(void *base, int64_t n, int64_t K1, int64_t P, BinWs &ws);
+bool bins_apply(int64_t P);
+hipError_t launch_binned(const double *w, const int32_t *T, int64_t n, const Tables &tb,
+                         const PriceDev &pr, const BinWs &ws, double *cost_out, int *status,
+                         hipStream_t stream);
+
 // Sorted path.
 struct SortWs {
     uint64_t *keys[2];
     int32_t *vals[2];
     uint32_t *hist;       // [256][nblocks]
     uint32_t *counts;     // [256] digit totals of the current pass
-    int64_t *Nsum;        // [n] inclusive prefix of T (sorted order), or the sums of T over
-                          // each run of 64 sorted positions when the closed form queries
+    int64_t *Nsum;        // [n] inclusive prefix of T (sorted order)
     double *Ssum;         // [n] the same for T*w
     int64_t *blkN;        // [nblocks_scan]
     double *blkS;         // [nblocks_scan]

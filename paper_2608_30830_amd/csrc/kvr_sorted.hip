@@ -20,11 +20,11 @@
 // written before it); from 2^22 keys each scatter also writes the next digit
 // as one byte per key, which the next histogram reads instead of the keys.
 //
-// Scans: the closed form needs N and S only at t1, at each deadline and at
-// the whole sample.  Without a requested order they are formed there, from
-// the scan tiles' exclusive prefixes and the sums of every run of 64 sorted
-// positions; with an order requested (or very many policies) the full
-// inclusive prefix arrays are written and read.
+// Scans: the full inclusive prefix arrays of T and T*w in sorted order, which
+// the closed form reads at t1, at each deadline and at the whole sample.
+//
+// Without a requested order the closed form needs no order either: grids of up
+// to 16,384 policies then take the per-bin sums of kvr_binned.hip instead.
 #include "kvr_device.h"
 #include "kvr_dpp.h"
 
@@ -612,16 +612,12 @@ __global__ void __launch_bounds__(kOneThreads) sort_small_kernel(
 // Per scan tile: sums of T and T*w over the sorted order.  GATHER: the sort's
 // payload is the base index (perm) and the context sizes are gathered through
 // it once, into Tsorted; otherwise the payload already is the context size in
-// sorted order (Tsorted) and is only read.  CHUNKS: the sums of every run of 64
-// sorted positions are also written (chunkN, chunkS; run c of tile b is
-// c = 32 b + 4 q + wave, the positions of row q that a wave holds), so that N
-// and S at a few query positions can be formed without the full prefix arrays.
-template <bool GATHER, bool CHUNKS>
+// sorted order (Tsorted) and is only read.
+template <bool GATHER>
 __global__ void __launch_bounds__(kScanThreads) scan_reduce_kernel(
     const uint64_t *__restrict__ skeys, const int32_t *__restrict__ perm,
     const int32_t *__restrict__ T, int64_t n, int64_t *__restrict__ blkN,
-    double *__restrict__ blkS, int32_t *__restrict__ Tsorted, int64_t *__restrict__ chunkN,
-    double *__restrict__ chunkS)
+    double *__restrict__ blkS, int32_t *__restrict__ Tsorted)
 {
     // striped over the tile (element q*256 + t of it), so that every load and
     // store of a wave covers consecutive positions; the tile's total is summed
@@ -648,24 +644,13 @@ __global__ void __launch_bounds__(kScanThreads) scan_reduce_kernel(
             en = t;
             es = (double)t * __longlong_as_double((long long)skeys[j]);
         }
-        if (CHUNKS) {   // this wave's 64 positions of row q (their sum in lane 63), then into the wave's total
-            en = wave_incl_scan(en);
-            es = wave_incl_scan(es);
-            const int64_t c = ((int64_t)blockIdx.x * kScanIPT + q) * (kScanThreads / kWave) + wave;
-            if (lane == kWave - 1 && c * kWave < n) {
-                chunkN[c] = en;
-                chunkS[c] = es;
-            }
-        }
         sn += en;
         ss += es;
     }
-    // fixed-order tree: wave_incl_scan's within each wave (done per chunk
-    // with CHUNKS), the total in lane 63, then the four waves in order
-    if (!CHUNKS) {
-        sn = wave_incl_scan(sn);
-        ss = wave_incl_scan(ss);
-    }
+    // fixed-order tree: wave_incl_scan's within each wave, the total in lane
+    // 63, then the four waves in order
+    sn = wave_incl_scan(sn);
+    ss = wave_incl_scan(ss);
     __shared__ int64_t rn[kScanThreads / kWave];
     __shared__ double rs[kScanThreads / kWave];
     if (lane == kWave - 1) {
@@ -868,24 +853,7 @@ __device__ __forceinline__ int64_t wave_upper_bound(const uint64_t *__restrict__
     return lo + __popcll(__ballot(le));
 }
 
-// The closed form of policy f for every load, from its two positions (counts of
-// sorted waits <= t1 and <= e); loads l0, l0 + lstep, ... are written.
-__device__ __forceinline__ void closed_form_values(int64_t tot, int64_t n1, int64_t ne, double s1,
-                                                   double se, int64_t n, const Tables &tb,
-                                                   const PriceDev &pr, int64_t f, double t1,
-                                                   double e, int l0, int lstep,
-                                                   double *__restrict__ cost)
-{
-    const int64_t P = (int64_t)tb.K1 * tb.K2;
-    const double hbm = s1 + t1 * (double)(tot - n1);
-    double hold = (se - s1) - t1 * (double)(ne - n1);
-    if (!isinf(e)) hold += (e - t1) * (double)(tot - ne);
-    const double fixed = pr.a1 * hbm + pr.b2 * (double)(ne - n1) + pr.b3 * (double)(tot - ne);
-    const double nd = (double)n;
-    for (int l = l0; l < tb.L; l += lstep) cost[(int64_t)l * P + f] = (fixed + tb.a2[l] * hold) / nd;
-}
-
-// The same from the inclusive prefix arrays.
+// closed_form_values from the inclusive prefix arrays.
 __device__ __forceinline__ void closed_form_policy(const int64_t *__restrict__ Nsum,
                                                    const double *__restrict__ Ssum, int64_t n,
                                                    const Tables &tb, const PriceDev &pr, int64_t f,
@@ -896,44 +864,6 @@ __device__ __forceinline__ void closed_form_policy(const int64_t *__restrict__ N
     const int64_t n1 = p1 ? Nsum[p1 - 1] : 0, ne = pe ? Nsum[pe - 1] : 0;
     const double s1 = p1 ? Ssum[p1 - 1] : 0.0, se = pe ? Ssum[pe - 1] : 0.0;
     closed_form_values(tot, n1, ne, s1, se, n, tb, pr, f, t1, e, l0, lstep, cost);
-}
-
-// N and S over the sorted positions [0, p), by one wave: the tile's exclusive
-// prefix, the 64-position chunk sums of the tile before p and the positions of
-// p's own chunk, each group added across the lanes in wave_total's fixed tree;
-// every lane returns the same values, and equal p give equal values.
-__device__ __forceinline__ void wave_prefix_at(int64_t p, int nb, const int64_t *__restrict__ blkN,
-                                               const double *__restrict__ blkS,
-                                               const int64_t *__restrict__ chunkN,
-                                               const double *__restrict__ chunkS,
-                                               const uint64_t *__restrict__ skeys,
-                                               const int32_t *__restrict__ Tsorted, int64_t &N,
-                                               double &S)
-{
-    const int lane = threadIdx.x % kWave;
-    int64_t tile = p / kScanTile;
-    if (tile > nb - 1) tile = nb - 1;
-    const int64_t off = p - tile * kScanTile;     // 0 .. kScanTile
-    const int nc = (int)(off / kWave), rem = (int)(off % kWave);
-    int64_t cn = 0, en = 0;
-    double cs = 0.0, es = 0.0;
-    if (lane < nc) {
-        const int64_t c = tile * (kScanTile / kWave) + lane;
-        cn = chunkN[c];
-        cs = chunkS[c];
-    }
-    if (lane < rem) {
-        const int64_t j = tile * kScanTile + (int64_t)nc * kWave + lane;
-        const int32_t t = Tsorted[j];
-        en = t;
-        es = (double)t * __longlong_as_double((long long)skeys[j]);
-    }
-    cn = wave_total(cn);
-    cs = wave_total(cs);
-    en = wave_total(en);
-    es = wave_total(es);
-    N = blkN[tile] + cn + en;
-    S = (blkS[tile] + cs) + es;
 }
 
 // One thread per policy (a, k): closed form for every load (many policies).
@@ -971,32 +901,6 @@ __global__ void __launch_bounds__(256) closed_form_wave_kernel(const uint64_t *_
     const int64_t p1 = wave_upper_bound(skeys, n, t1);
     const int64_t pe = wave_upper_bound(skeys, n, e);
     closed_form_policy(Nsum, Ssum, n, tb, pr, f, t1, e, p1, pe, (int)(threadIdx.x % kWave), kWave,
-                       cost);
-}
-
-// One wave per policy, N and S at the query positions only (no prefix arrays):
-// the two positions by 64-ary searches, then wave_prefix_at for t1, the
-// deadline and the whole sample.
-__global__ void __launch_bounds__(256) closed_form_query_kernel(
-    const uint64_t *__restrict__ skeys, const int32_t *__restrict__ Tsorted, int64_t n, int nb,
-    const int64_t *__restrict__ blkN, const double *__restrict__ blkS,
-    const int64_t *__restrict__ chunkN, const double *__restrict__ chunkS, Tables tb, PriceDev pr,
-    double *__restrict__ cost)
-{
-    const int64_t P = (int64_t)tb.K1 * tb.K2;
-    const int64_t f = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-    if (f >= P) return;   // uniform per wave
-    const int a = (int)(f / tb.K2), k = (int)(f % tb.K2);
-    const double t1 = tb.t1[a];
-    const double e = t1 + tb.t2[k];
-    const int64_t p1 = wave_upper_bound(skeys, n, t1);
-    const int64_t pe = wave_upper_bound(skeys, n, e);
-    int64_t tot, n1, ne;
-    double sall, s1, se;
-    wave_prefix_at(n, nb, blkN, blkS, chunkN, chunkS, skeys, Tsorted, tot, sall);
-    wave_prefix_at(p1, nb, blkN, blkS, chunkN, chunkS, skeys, Tsorted, n1, s1);
-    wave_prefix_at(pe, nb, blkN, blkS, chunkN, chunkS, skeys, Tsorted, ne, se);
-    closed_form_values(tot, n1, ne, s1, se, n, tb, pr, f, t1, e, (int)(threadIdx.x % kWave), kWave,
                        cost);
 }
 
@@ -1116,29 +1020,12 @@ hipError_t launch_sorted_path(const double *w, const int32_t *T, int64_t n, cons
     hipError_t err = launch_sort(w, T, n, ws, want_perm ? 0 : 1, status, stream);
     if (err != hipSuccess) return err;
     int32_t *Tsorted = want_perm ? ws.vals[1] : ws.vals[0];   // buffer 1 is free after the sort
-    const int64_t P = (int64_t)tb.K1 * tb.K2;
-    if (!want_perm && P <= kWavePolicies) {
-        // N and S are needed at 2 P + 1 positions only: the tile sums, the
-        // 64-position chunk sums (in the prefix arrays' space) and the tiles'
-        // prefixes, then one wave per policy; no prefix arrays are written
-        hipLaunchKernelGGL((scan_reduce_kernel<false, true>), dim3(ws.nblocks_scan),
-                           dim3(kScanThreads), 0, stream, ws.keys[0], nullptr, T, n, ws.blkN,
-                           ws.blkS, Tsorted, ws.Nsum, ws.Ssum);
-        hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(1024), 0, stream, ws.blkN, ws.blkS,
-                           ws.nblocks_scan);
-        hipLaunchKernelGGL(closed_form_query_kernel, dim3((unsigned)cdiv(P, 256 / kWave)),
-                           dim3(256), 0, stream, ws.keys[0], Tsorted, n, ws.nblocks_scan, ws.blkN,
-                           ws.blkS, ws.Nsum, ws.Ssum, tb, pr, cost_out);
-        return hipGetLastError();
-    }
     if (want_perm)
-        hipLaunchKernelGGL((scan_reduce_kernel<true, false>), dim3(ws.nblocks_scan),
-                           dim3(kScanThreads), 0, stream, ws.keys[0], ws.vals[0], T, n, ws.blkN,
-                           ws.blkS, Tsorted, nullptr, nullptr);
+        hipLaunchKernelGGL(scan_reduce_kernel<true>, dim3(ws.nblocks_scan), dim3(kScanThreads), 0,
+                           stream, ws.keys[0], ws.vals[0], T, n, ws.blkN, ws.blkS, Tsorted);
     else
-        hipLaunchKernelGGL((scan_reduce_kernel<false, false>), dim3(ws.nblocks_scan),
-                           dim3(kScanThreads), 0, stream, ws.keys[0], nullptr, T, n, ws.blkN,
-                           ws.blkS, Tsorted, nullptr, nullptr);
+        hipLaunchKernelGGL(scan_reduce_kernel<false>, dim3(ws.nblocks_scan), dim3(kScanThreads), 0,
+                           stream, ws.keys[0], nullptr, T, n, ws.blkN, ws.blkS, Tsorted);
     hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(1024), 0, stream, ws.blkN, ws.blkS,
                        ws.nblocks_scan);
     hipLaunchKernelGGL(scan_final_kernel, dim3(ws.nblocks_scan), dim3(kScanThreads), 0, stream,
