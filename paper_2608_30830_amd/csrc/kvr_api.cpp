@@ -415,7 +415,7 @@ int kvr::cost_grid_entry(const double *d_wait_s, const int32_t *d_ctx_tokens, in
         off_sort = off_a2 + align256(sizeof(double) * Lpad);
         // the same workspace with and without a requested order
         need = kvr::sort_ws_bytes(n);
-        if (kvr::bins_apply(P)) need = std::max(need, kvr::bin_ws_bytes(g->n_t1, P));
+        if (kvr::bins_apply(P)) need = std::max(need, kvr::bin_ws_bytes(n, g->n_t1, P));
         need += off_sort;
     }
     if (d_ws == nullptr) {
@@ -473,7 +473,10 @@ int kvr::cost_grid_entry(const double *d_wait_s, const int32_t *d_ctx_tokens, in
     KVR_MARK(g_prof_begin, s);
     if (d_perm == nullptr && kvr::bins_apply(P)) {
         kvr::BinWs bws{};
-        kvr::bin_ws_carve(at<char>(d_ws, off_sort), n, g->n_t1, P, bws);
+        double last = g->t2[g->n_t2 - 1];
+        if (std::isinf(last)) last = g->n_t2 > 1 ? g->t2[g->n_t2 - 2] : 0.0;
+        kvr::bin_ws_carve(at<char>(d_ws, off_sort), n, g->n_t1, P,
+                          std::fabs(g->t1[g->n_t1 - 1]) + last, bws);
         KVR_TRY(kvr::launch_binned(d_wait_s, d_ctx_tokens, n, tb, pr, bws, d_cost, status, s));
         KVR_MARK(g_prof_end, s);
         return KVR_OK;

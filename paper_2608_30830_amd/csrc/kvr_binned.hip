@@ -21,7 +21,7 @@
 // edge, and every wait has an upper edge.
 //
 // Measured on MI355X, the whole call against the sort: 2^24 waits and 66
-// thresholds 95 us against 1,092 (the sums 87 us, 2.3 TB/s); 100,003 waits and
+// thresholds 68 us against 1,092 (the sums 56 us, 3.6 TB/s); 100,003 waits and
 // 510 thresholds 31 us against 104 (28 launches of 3-5 us each, four now).
 #include "kvr_device.h"
 #include "kvr_dpp.h"
@@ -35,7 +35,9 @@ constexpr int64_t kBinChunk = 65536;       // waits per block at most: 48-bit li
 constexpr int64_t kBinBlocks = 512;        // blocks that fill the chip (two to a CU)
 constexpr int kBinFused = 4096;            // bins that the closed form's own blocks scan
 constexpr int kBinWords = 4;               // per bin: sum of T, then three 32-bit limbs of S
+constexpr int kBinCopies = 8;              // of every bin, while a block scans them all itself
 constexpr int kFixedEdges = 211;           // 2^-1070, 2^-1060, ..., 2^1020, the largest finite
+constexpr int kBuckets = 512;              // search table: 16 buckets per binade, 32 binades
 constexpr int kBinLdsTable = 4096;         // timer-table entries staged in LDS
 constexpr int kItemLanes = 8;              // lanes per threshold
 constexpr int kFormPolicies = 64;          // policies of one closed-form block
@@ -57,15 +59,26 @@ static int64_t bin_chunk(int64_t n)
 // each of which reads the sample once.
 bool bins_apply(int64_t P) { return P <= 16384; }
 
-size_t bin_ws_bytes(int64_t K1, int64_t P)
+// Global copies of each bin, block q of the sums adding into copy q % copies:
+// with one copy the atomics of 512 blocks on the same few addresses took 28 us
+// of a 2^24-wait call with 66 thresholds (90 us; 68 with eight copies).  Reading
+// eight copies costs the closed form's blocks 5 us at 723 bins, more than the
+// adds of 98 blocks do (100,003 waits); grids of more bins spread the adds by
+// themselves.
+static int bin_copies(int64_t n, int64_t bins)
+{
+    return bins <= kBinFused && cdiv(n, bin_chunk(n)) > 128 ? kBinCopies : 1;
+}
+
+size_t bin_ws_bytes(int64_t n, int64_t K1, int64_t P)
 {
     const int64_t M = K1 + P + kFixedEdges;
     return align256(sizeof(double) * (M + 1)) + align256(sizeof(int32_t) * (K1 + P)) +
-           align256(sizeof(uint64_t) * kBinWords * (M + 1)) +
+           align256(sizeof(uint64_t) * kBinWords * bin_copies(n, M + 1) * (M + 1)) +
            2 * align256(sizeof(double) * (M + 1));
 }
 
-void bin_ws_carve(void *base, int64_t n, int64_t K1, int64_t P, BinWs &ws)
+void bin_ws_carve(void *base, int64_t n, int64_t K1, int64_t P, double largest, BinWs &ws)
 {
     char *p = static_cast<char *>(base);
     auto take = [&](size_t bytes) {
@@ -75,10 +88,15 @@ void bin_ws_carve(void *base, int64_t n, int64_t K1, int64_t P, BinWs &ws)
     };
     ws.M = (int)(K1 + P) + kFixedEdges;
     ws.chunk = bin_chunk(n);
+    uint64_t bits;
+    __builtin_memcpy(&bits, &largest, 8);
+    const int top = (int)(bits >> 48);   // largest >= 0
+    ws.bucket0 = top > kBuckets - 1 ? top - (kBuckets - 1) : 0;
     ws.nblocks = (int)cdiv(n, ws.chunk);
     ws.thr = (double *)take(sizeof(double) * (ws.M + 1));
     ws.at = (int32_t *)take(sizeof(int32_t) * (K1 + P));
-    ws.bins = (unsigned long long *)take(sizeof(uint64_t) * kBinWords * (ws.M + 1));
+    ws.copies = bin_copies(n, ws.M + 1);
+    ws.bins = (unsigned long long *)take(sizeof(uint64_t) * kBinWords * ws.copies * (ws.M + 1));
     ws.cumN = (int64_t *)take(sizeof(int64_t) * (ws.M + 1));
     ws.cumS = (double *)take(sizeof(double) * (ws.M + 1));
 }
@@ -112,7 +130,8 @@ __global__ void __launch_bounds__(256) bin_thresholds_kernel(Tables tb, BinWs ws
     const int lane = (int)threadIdx.x % kItemLanes;
     const int i = (int)(blockIdx.x * (blockDim.x / kItemLanes) + threadIdx.x / kItemLanes);
     if (i > ws.M) return;   // whole groups of lanes
-    if (lane < kBinWords) ws.bins[(int64_t)i * kBinWords + lane] = 0ull;
+    for (int q = lane; q < kBinWords * ws.copies; q += kItemLanes)
+        ws.bins[(int64_t)i * kBinWords * ws.copies + q] = 0ull;
     if (i == ws.M) {
         if (lane == 0) ws.thr[i] = INFINITY;
         return;
@@ -160,7 +179,13 @@ __global__ void __launch_bounds__(256) bin_thresholds_kernel(Tables tb, BinWs ws
 // [b0, b0 + nb) are added to the range's bins in LDS, then to the global ones.
 // RP is the power of two above the number of bins (kBinRange + 1 at most): edge[0]
 // is the range's lower edge, edge[1 + i] the upper edge of bin b0 + i, and
-// from edge[1 + nb] on infinity, so that the search needs no bounds.
+// from edge[1 + nb] on infinity.
+//
+// A wait's bin is searched between the edges of its bucket, the upper 16 bits
+// of its binary64 word (16 buckets a binade, the top one holding the grid's
+// largest timer; waits below or above take the end buckets): zero to three
+// dependent LDS reads for grids of 64 to 1,024 log-spaced timers in place of
+// log2(RP) (2^24 waits, nine steps: 87 -> 79 us).
 template <int RP>
 __global__ void __launch_bounds__(kBinThreads) bin_sums_kernel(const double *__restrict__ w,
                                                                const int32_t *__restrict__ T,
@@ -169,11 +194,26 @@ __global__ void __launch_bounds__(kBinThreads) bin_sums_kernel(const double *__r
 {
     __shared__ double edge[RP + 1];
     __shared__ unsigned long long sumT[RP], lo48[RP], hi48[RP];
+    __shared__ uint16_t first[kBuckets + 1];
     const int range = (int)(blockIdx.x % nranges);
     const int64_t chunk = blockIdx.x / nranges;
     const int b0 = range * kBinRange;
     const int total = ws.M + 1;                       // bins 0..M
     const int nb = total - b0 < kBinRange ? total - b0 : kBinRange;
+    const int64_t j0 = chunk * ws.chunk;
+    const int64_t j1 = j0 + ws.chunk < n ? j0 + ws.chunk : n;
+    double x[kBinIlp];
+    int32_t t[kBinIlp];
+    auto fetch = [&](int64_t jb) {   // positions past the chunk re-read its last wait
+#pragma unroll
+        for (int u = 0; u < kBinIlp; ++u) {
+            const int64_t j = jb + u * kBinThreads;
+            const int64_t jc = j < j1 ? j : j1 - 1;
+            x[u] = w[jc];
+            t[u] = T[jc];
+        }
+    };
+    fetch(j0 + threadIdx.x);   // in flight while the tables are set up
     for (int q = threadIdx.x; q < RP; q += kBinThreads) {
         edge[q + 1] = q < nb ? ws.thr[b0 + q] : INFINITY;
         sumT[q] = lo48[q] = hi48[q] = 0ull;
@@ -183,20 +223,22 @@ __global__ void __launch_bounds__(kBinThreads) bin_sums_kernel(const double *__r
     if (threadIdx.x == 0) edge[0] = b0 > 0 ? ws.thr[b0 - 1] : -1.0;
     __syncthreads();
     const double lower = edge[0], upper = edge[nb];   // of the whole range
-    const int64_t j0 = chunk * ws.chunk;
-    const int64_t j1 = j0 + ws.chunk < n ? j0 + ws.chunk : n;
+    // first[b] = edges of the range (from edge[1] on) below every value of bucket b
+    const int base0 = ws.bucket0;
+    if ((int)threadIdx.x <= kBuckets) {
+        const int b = threadIdx.x;
+        const double v = __longlong_as_double((long long)((uint64_t)(base0 + b) << 48));
+        int pos = 0;
+        for (int step = RP / 2; step > 0; step >>= 1)   // pos + step < RP
+            if (edge[pos + step] < v) pos += step;
+        first[b] = (uint16_t)(b == 0 ? 0 : b == kBuckets || pos > nb - 1 ? nb - 1 : pos);
+    }
+    __syncthreads();
     bool bad = false;
     for (int64_t jb = j0 + threadIdx.x; jb < j1; jb += kBinIlp * kBinThreads) {
-        double x[kBinIlp];
-        int32_t t[kBinIlp];
-        int pos[kBinIlp];
-#pragma unroll
-        for (int u = 0; u < kBinIlp; ++u) {   // every load in flight before the searches
-            const int64_t j = jb + u * kBinThreads;
-            const int64_t jc = j < j1 ? j : j1 - 1;
-            x[u] = w[jc];
-            t[u] = T[jc];
-        }
+        if (jb != j0 + threadIdx.x) fetch(jb);
+        int pos[kBinIlp], hi[kBinIlp];
+        bool in[kBinIlp], more = false;
 #pragma unroll
         for (int u = 0; u < kBinIlp; ++u) {
             const uint64_t bits = (uint64_t)__double_as_longlong(x[u]);
@@ -208,17 +250,28 @@ __global__ void __launch_bounds__(kBinThreads) bin_sums_kernel(const double *__r
                 bad = true;
                 t[u] = 1;
             }
-            pos[u] = 0;
+            x[u] += 0.0;                                   // -0.0 -> +0.0
+            in[u] = jb + u * kBinThreads < j1 && x[u] > lower && x[u] <= upper;
+            const int b = (int)((uint64_t)__double_as_longlong(x[u]) >> 48) - base0;
+            const int bc = b < 0 ? 0 : b < kBuckets ? b : kBuckets - 1;
+            pos[u] = first[bc];
+            hi[u] = in[u] ? (int)first[bc + 1] : pos[u];
+            more |= pos[u] < hi[u];
         }
+        while (__any(more)) {   // the number of edges below x lies in [pos, hi]
+            more = false;
 #pragma unroll
-        for (int step = RP / 2; step > 0; step >>= 1) {   // edges of the range below x
-#pragma unroll
-            for (int u = 0; u < kBinIlp; ++u)
-                if (edge[pos[u] + step] < x[u]) pos[u] += step;
+            for (int u = 0; u < kBinIlp; ++u) {
+                const int mid = (pos[u] + hi[u]) >> 1;
+                const bool open = pos[u] < hi[u], below = edge[mid + 1] < x[u];
+                pos[u] = open && below ? mid + 1 : pos[u];
+                hi[u] = open && !below ? mid : hi[u];
+                more |= pos[u] < hi[u];
+            }
         }
 #pragma unroll
         for (int u = 0; u < kBinIlp; ++u) {
-            if (jb + u * kBinThreads >= j1 || !(x[u] > lower && x[u] <= upper)) continue;
+            if (!in[u]) continue;
             const double top = edge[pos[u] + 1];
             atomicAdd(&sumT[pos[u]], (unsigned long long)t[u]);
             double base = edge[pos[u]];
@@ -241,7 +294,8 @@ __global__ void __launch_bounds__(kBinThreads) bin_sums_kernel(const double *__r
     __syncthreads();
     for (int q = threadIdx.x; q < nb; q += kBinThreads) {
         if (sumT[q] == 0ull) continue;
-        unsigned long long *out = ws.bins + (int64_t)(b0 + q) * kBinWords;
+        unsigned long long *out =
+            ws.bins + ((int64_t)(b0 + q) * ws.copies + blockIdx.x % ws.copies) * kBinWords;
         atomicAdd(out, sumT[q]);
         const uint64_t lo = lo48[q], hi = hi48[q];
         // hi * 2^48 + lo as three 32-bit limbs (the last with the carries)
@@ -269,7 +323,11 @@ __device__ __forceinline__ void bin_prefix(const BinWs &ws, NOut *cumN, SOut *cu
     const int per = (total + kBinThreads - 1) / kBinThreads;
     const int q0 = t * per, q1 = q0 + per < total ? q0 + per : total;
     auto bin_of = [&](int b, int64_t &N, double &S) {
-        const unsigned long long *in = ws.bins + (int64_t)b * kBinWords;
+        const unsigned long long *from = ws.bins + (int64_t)b * kBinWords * ws.copies;
+        unsigned long long in[kBinWords] = {0ull, 0ull, 0ull, 0ull};
+        for (int c = 0; c < ws.copies; ++c)
+#pragma unroll
+            for (int q = 0; q < kBinWords; ++q) in[q] += from[c * kBinWords + q];
         N = (int64_t)in[0];
         const double base = b > 0 ? ws.thr[b - 1] : 0.0, top = ws.thr[b];
         if (isinf(top)) {   // no finite wait lies beyond the last fixed edge
@@ -290,6 +348,8 @@ __device__ __forceinline__ void bin_prefix(const BinWs &ws, NOut *cumN, SOut *cu
         int64_t N;
         double S;
         bin_of(b, N, S);
+        cumN[b] = N;   // read back below
+        cumS[b] = S;
         sn += N;
         ss += S;
         if (N != 0) last = b;
@@ -316,11 +376,9 @@ __device__ __forceinline__ void bin_prefix(const BinWs &ws, NOut *cumN, SOut *cu
     const int back = __shfl_up(xl, 1, kWave);   // every lane takes part
     if (lane > 0 && back > pl) pl = back;
     for (int b = q0; b < q1; ++b) {
-        int64_t N;
-        double S;
-        bin_of(b, N, S);
+        const int64_t N = cumN[b];
         pn += N;
-        ps += S;
+        ps += cumS[b];
         cumN[b] = pn;
         if (N != 0) cumS[b] = ps;
     }
@@ -375,9 +433,7 @@ hipError_t launch_binned(const double *w, const int32_t *T, int64_t n, const Tab
     hipLaunchKernelGGL(bin_thresholds_kernel, dim3((unsigned)cdiv(total, 256 / kItemLanes)),
                        dim3(256), 0, stream, tb, ws);
     const dim3 grid((unsigned)(ws.nblocks * nranges)), block(kBinThreads);
-    if (total < 128)
-        hipLaunchKernelGGL(bin_sums_kernel<128>, grid, block, 0, stream, w, T, n, ws, nranges, status);
-    else if (total < 512)
+    if (total < 512)
         hipLaunchKernelGGL(bin_sums_kernel<512>, grid, block, 0, stream, w, T, n, ws, nranges, status);
     else if (total < 2048)
         hipLaunchKernelGGL(bin_sums_kernel<2048>, grid, block, 0, stream, w, T, n, ws, nranges, status);

@@ -181,16 +181,19 @@ struct BinWs {
     double *thr;                // [M + 1] the grid's t1 timers and deadlines and the fixed edges in
                                 // order, then inf
     int32_t *at;                // [K1 + P] thresholds strictly below each timer, then each deadline
-    unsigned long long *bins;   // [M + 1][4] sums over the waits of each bin
+    unsigned long long *bins;   // [M + 1][copies][4] sums over the waits of each bin
     int64_t *cumN;              // [M + 1] prefix sums over the bins (grids of many policies)
     double *cumS;
     int M;                      // thresholds
+    int copies;                 // of each bin
+    int bucket0;                // first bucket of the search table
     int nblocks;                // chunks of the sample
     int64_t chunk;              // waits per chunk
 };
 
-size_t bin_ws_bytes(int64_t K1, int64_t P);
-void bin_ws_carve(void *base, int64_t n, int64_t K1, int64_t P, BinWs &ws);
+size_t bin_ws_bytes(int64_t n, int64_t K1, int64_t P);
+// largest: the largest finite deadline of the grid, or any time of its scale.
+void bin_ws_carve(void *base, int64_t n, int64_t K1, int64_t P, double largest, BinWs &ws);
 bool bins_apply(int64_t P);
 hipError_t launch_binned(const double *w, const int32_t *T, int64_t n, const Tables &tb,
                          const PriceDev &pr, const BinWs &ws, double *cost_out, int *status,
