@@ -599,6 +599,8 @@ int kvr_bootstrap_factored(const double *d_wait_s, const int32_t *d_ctx_tokens, 
     const size_t off_rank = take(sizeof(int32_t) * n);
     const size_t off_Ts = take(sizeof(int32_t) * n);
     const size_t off_sw = take(sizeof(double) * n);
+    const bool small = kvr::factored_small(n, m);
+    const size_t off_cpos = take(small ? sizeof(uint32_t) * n : 0);
     const size_t off_u1 = take(sizeof(int32_t) * g->n_t1);
     const size_t off_ue = take(sizeof(int32_t) * P);
     const size_t off_qslot = take(sizeof(int32_t) * (n + 1));
@@ -624,6 +626,7 @@ int kvr_bootstrap_factored(const double *d_wait_s, const int32_t *d_ctx_tokens, 
     fw.rank = at<int32_t>(d_ws, off_rank);
     fw.Ts = at<int32_t>(d_ws, off_Ts);
     fw.sw = at<double>(d_ws, off_sw);
+    fw.cpos = small ? at<uint32_t>(d_ws, off_cpos) : nullptr;
     fw.u1 = at<int32_t>(d_ws, off_u1);
     fw.ue = at<int32_t>(d_ws, off_ue);
     fw.qslot = at<int32_t>(d_ws, off_qslot);

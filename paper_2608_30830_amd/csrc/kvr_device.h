@@ -57,7 +57,7 @@ __device__ __forceinline__ V wave_sum(V v)
 // Total order used by every selection: smaller cost first, then larger f.
 __device__ __forceinline__ void argmin_merge(double &bc, int32_t &bf, double oc, int32_t of)
 {
-    bool take = (oc < bc) || (oc == bc && of > bf);
+    const bool take = (oc < bc) | ((oc == bc) & (of > bf));
     bc = take ? oc : bc;
     bf = take ? of : bf;
 }

@@ -18,7 +18,10 @@
 //
 // Once per call: the base waits are radix-sorted; each t1 and each deadline
 // gets its count of waits at or below it (a sorted position, a query), and
-// the distinct query positions are numbered in order (slots).  Per batch of
+// the distinct query positions are numbered in order (slots).  (The queries
+// need no order within a bin of the deadlines, but the sums' roundings follow
+// it, and where a resample holds no wait between two deadlines the selection
+// between them hangs on those roundings.)  Per batch of
 // resamples: factored_prefix_kernel (one block per resample, four per CU: the
 // draws' multiplicities per base sample in LDS, then, from LDS, a fixed-order
 // scan of the weights c_k T_k (exact) and c_k T_k w_k over the positions that
@@ -41,84 +44,63 @@ constexpr int kFScanPer = 8;            // consecutive positions per thread in t
 constexpr int kFUnroll = 8;             // draws per thread and step, fetched together
 constexpr int kFLoads = 32;             // loads per policy-kernel block (16 when L <= 16)
 constexpr int kFPolThreads = 256;
-// Policies per thread and step in the policy kernel: 4 with 32-load tiles (two
-// policies' dependent gathers more in flight, at the same three waves per
-// SIMD), 2 with 16-load tiles (where 4 would cost a wave).
-template <int FL> constexpr int kFPU = FL == 16 ? 2 : 4;
 // Draws per resample up to which every N sum (m times a context size below
 // 2^31) is an integer below 2^53, exact in double.
 constexpr int64_t kFExactDoubleDraws = int64_t(1) << 22;
 
-// One step of a wave arg-min by DPP: the (cost, index) pair CTRL names is
-// merged into this lane's under the library's total order; a lane the
-// control gives no source (or masks off) reads the identity (+inf, -1).
-template <int CTRL, int ROWM>
-__device__ __forceinline__ void dpp_argmin_step(double &c, int32_t &f)
-{
-    const double oc = dpp_move<CTRL, ROWM>(c, 0x7ff0000000000000ull);
-    const int32_t of = dpp_move<CTRL, ROWM>(f, 0xffffffffull);
-    argmin_merge(c, f, oc, of);
-}
-
-// Arg-min of (c, f) over the 64 lanes of a wave, left in lane 63: the steps
-// of wave_incl_scan with the merge for the sum (the total order makes the
-// result independent of the merge order).
-__device__ __forceinline__ void wave_argmin_dpp(double &c, int32_t &f)
-{
-    dpp_argmin_step<kDppRowShr1, 0xf>(c, f);
-    dpp_argmin_step<kDppRowShr2, 0xf>(c, f);
-    dpp_argmin_step<kDppRowShr4, 0xf>(c, f);
-    dpp_argmin_step<kDppRowShr8, 0xf>(c, f);
-    dpp_argmin_step<kDppRowBcast15, 0xa>(c, f);
-    dpp_argmin_step<kDppRowBcast31, 0xc>(c, f);
-}
-
-// Per sorted position k: the sorted wait and the context size there (below
-// 1 counts as 1; the sort has flagged it); per base sample: its
-// sorted position.
-__global__ void __launch_bounds__(256) factored_rank_kernel(const uint64_t *__restrict__ skeys,
-                                                            const int32_t *__restrict__ perm,
-                                                            const int32_t *__restrict__ T, int64_t n,
-                                                            double *__restrict__ sw,
-                                                            int32_t *__restrict__ Ts,
-                                                            int32_t *__restrict__ rank)
-{
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const int32_t i = perm[k];
-    sw[k] = __longlong_as_double((long long)skeys[k]);
-    int32_t t = T[i];
-    Ts[k] = t < 1 ? 1 : t;
-    rank[i] = (int32_t)k;
-}
-
 // Number of sorted waits <= x.
-__device__ __forceinline__ int32_t count_le(const double *__restrict__ sw, int64_t n, double x)
+__device__ __forceinline__ int32_t count_le(const uint64_t *__restrict__ skeys, int64_t n, double x)
 {
     int64_t lo = 0, hi = n;
     while (lo < hi) {
         const int64_t mid = lo + (hi - lo) / 2;
-        if (sw[mid] <= x) lo = mid + 1;
+        if (__longlong_as_double((long long)skeys[mid]) <= x) lo = mid + 1;
         else hi = mid;
     }
     return (int32_t)lo;
 }
 
-// Items 0..K1-1: u1[a] = #(w <= t1[a]); items K1..K1+P-1: ue[f] = #(w <= e_f).
-__global__ void __launch_bounds__(256) factored_bounds_kernel(const double *__restrict__ sw,
-                                                              int64_t n, Tables tb,
-                                                              int32_t *__restrict__ u1,
-                                                              int32_t *__restrict__ ue)
+// Items 0..n-1, per sorted position k: the sorted wait and the context size
+// there (below 1 counts as 1; the sort has flagged it) and, per base sample, its
+// sorted position; with cpos the place of the sample's counter in
+// factored_prefix_small_kernel.  Items n..n+K1-1:
+// u1[a] = #(w <= t1[a]); then P items: ue[f] = #(w <= e_f).  Both are
+// marked in the position bitmask.
+__global__ void __launch_bounds__(256) factored_rank_kernel(
+    const uint64_t *__restrict__ skeys, const int32_t *__restrict__ perm,
+    const int32_t *__restrict__ T, int64_t n, Tables tb, double *__restrict__ sw,
+    int32_t *__restrict__ Ts, int32_t *__restrict__ rank, uint32_t *__restrict__ cpos,
+    int32_t *__restrict__ u1, int32_t *__restrict__ ue,
+    uint32_t *__restrict__ qbits)
 {
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t P = (int64_t)tb.K1 * tb.K2;
-    if (g < tb.K1) {
-        u1[g] = count_le(sw, n, tb.t1[g]);
-    } else if (g - tb.K1 < P) {
-        const int64_t f = g - tb.K1;
-        const int a = (int)(f / tb.K2), k = (int)(f % tb.K2);
-        ue[f] = count_le(sw, n, tb.t1[a] + tb.t2[k]);
+    if (k < n) {
+        const int32_t i = perm[k];
+        sw[k] = __longlong_as_double((long long)skeys[k]);
+        const int32_t t = T[i];
+        Ts[k] = t < 1 ? 1 : t;
+        rank[i] = (int32_t)k;
+        if (cpos != nullptr) {   // uniform: n <= 65,536
+            const uint32_t ui = (uint32_t)i;
+            cpos[k] = ((ui >> 1) & 0x7ffcu) | ((ui & 7u) << 18);
+        }
+        return;
     }
+    const int64_t g = k - n;
+    if (g >= tb.K1 + P) return;
+    double x;
+    if (g < tb.K1) {
+        x = tb.t1[g];
+    } else {
+        const int64_t f = g - tb.K1;
+        const int a = (int)(f / tb.K2), c = (int)(f % tb.K2);
+        x = tb.t1[a] + tb.t2[c];
+    }
+    const int32_t q = count_le(skeys, n, x);
+    if (g < tb.K1) u1[g] = q;
+    else ue[g - tb.K1] = q;
+    atomicOr(&qbits[q >> 5], 1u << (q & 31));
 }
 
 __global__ void __launch_bounds__(256) factored_fill_kernel(uint32_t *__restrict__ qbits,
@@ -126,19 +108,6 @@ __global__ void __launch_bounds__(256) factored_fill_kernel(uint32_t *__restrict
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < nwords) qbits[i] = 0u;
-}
-
-// Marks every query position: bit k of the position bitmask.
-__global__ void __launch_bounds__(256) factored_mark_kernel(const int32_t *__restrict__ u1,
-                                                            const int32_t *__restrict__ ue,
-                                                            int32_t K1, int64_t P,
-                                                            uint32_t *__restrict__ qbits)
-{
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t k = -1;
-    if (g < K1) k = u1[g];
-    else if (g - K1 < P) k = ue[g - K1];
-    if (k >= 0) atomicOr(&qbits[k >> 5], 1u << (k & 31));
 }
 
 // One block: qbase[w] = the marked positions in words 0 .. w-1 (an exclusive
@@ -408,19 +377,330 @@ __global__ void __launch_bounds__(kFPThreads) factored_prefix_kernel(
     }
 }
 
+// The same rows for base samples of at most 65,536 (every 4-bit counter of a
+// resample in LDS at once) and double N sums, with what the scan reads per
+// position made ready: cpos[k] = byte address of the counter word of the base
+// sample at sorted position k | its bit << 16.  A draw is five VALU operations
+// and an LDS add, a position a 4-bit extract, two conversions and six fp64
+// operations, everything in 32-bit indices; the rows are read 16
+// bytes a lane from the first aligned draw on.  A wave's query slots are
+// consecutive, so their records are gathered in LDS and stored as one run
+// (up to kFStage of them, else one by one): scattered 16-byte stores took 200 of
+// 660 us on the two-tier call (4,096 rows of 65,536 draws).  The draws alone
+// take 189 us; the scan is bound by its VALU operations and the chain of each
+// tile (reads, wave scans, barrier).  Two-tier: 786 us in
+// factored_prefix_kernel, 580 us here.  Two resamples per block that share the
+// reads measured the same, and the next tile's reads in flight 3 % less there but
+// with a block less per CU (141 VGPRs) 5 % more at 1,024 rows.
+//
+// A wrapped counter is found as above (the decoded total differs from m); the
+// resample is then counted again by sorted position with 32-bit counters,
+// kFLdsWords positions per pass.
+constexpr int kFStage = 108;   // records per wave: four blocks of 39.5 KiB per CU
+
+__global__ void __launch_bounds__(kFPThreads) factored_prefix_small_kernel(
+    const int32_t *__restrict__ idx, int n, int m, int64_t r0, const int32_t *__restrict__ rank,
+    const uint32_t *__restrict__ cpos, const int32_t *__restrict__ Ts,
+    const double *__restrict__ sw, const uint32_t *__restrict__ qbits,
+    const int32_t *__restrict__ qbase, int nqs, double2 *__restrict__ TQ,
+    unsigned long long *__restrict__ tot, int *status)
+{
+    constexpr int nw = kFPThreads / kWave;
+    constexpr int kTile = kFPThreads * kFScanPer;
+    __shared__ uint32_t lh[kFLdsWords];
+    __shared__ double2 wtot[2][nw];
+    __shared__ double2 stage[nw][kFStage];
+    __shared__ int wchk[nw];
+    const int64_t rb = blockIdx.x;
+    const int32_t *row = idx + (r0 + rb) * m;
+    double2 *qrow = TQ + rb * nqs;
+    const int t = threadIdx.x, lane = t % kWave, wv = t / kWave;
+    double carry_n = 0.0, carry_s = 0.0;   // totals of the earlier positions (same in every thread)
+    int parity = 0;
+
+    // past one position, rounded as factored_prefix_kernel rounds (the product,
+    // then the sum)
+    auto advance = [](double &pn, double &ps, double cw, double w) {
+#pragma clang fp contract(off)
+        const double s = cw * w;
+        pn = pn + cw;
+        ps = ps + s;
+    };
+    // scan of positions [p0, p1), count(k, packed) the multiplicity at position k
+    auto scan = [&](int p0, int p1, auto count) {
+        for (int base = p0; base < p1; base += kTile) {
+            const int k0 = base + t * kFScanPer;
+            double w[kFScanPer], cw[kFScanPer];
+            int32_t Ti[kFScanPer];
+            uint32_t cp[kFScanPer];
+            // marks of the 8 positions (k0 is a multiple of 8) and the slot of the first
+            const int kw = (k0 < p1 ? k0 : p1 - 1) >> 5;
+            const uint32_t word = qbits[kw];
+            const int32_t wbase = qbase[kw];
+            if (k0 + kFScanPer <= p1) {   // k0 is a multiple of 8: 16-byte loads
+#pragma unroll
+                for (int h = 0; h < kFScanPer; h += 4) {
+                    const uint4 c4 = *reinterpret_cast<const uint4 *>(cpos + k0 + h);
+                    const int4 t4 = *reinterpret_cast<const int4 *>(Ts + k0 + h);
+                    cp[h] = c4.x; cp[h + 1] = c4.y; cp[h + 2] = c4.z; cp[h + 3] = c4.w;
+                    Ti[h] = t4.x; Ti[h + 1] = t4.y; Ti[h + 2] = t4.z; Ti[h + 3] = t4.w;
+                }
+#pragma unroll
+                for (int h = 0; h < kFScanPer; h += 2) {
+                    const double2 w2 = *reinterpret_cast<const double2 *>(sw + k0 + h);
+                    w[h] = w2.x; w[h + 1] = w2.y;
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < kFScanPer; ++q) {
+                    const bool in = k0 + q < p1;
+                    const int k = in ? k0 + q : p1 - 1;
+                    cp[q] = cpos[k];
+                    Ti[q] = in ? Ts[k] : 0;
+                    w[q] = in ? sw[k] : 0.0;
+                }
+            }
+            double tn = 0.0, ts = 0.0;
+#pragma unroll
+            for (int q = 0; q < kFScanPer; ++q) {
+                const int k = k0 + q < p1 ? k0 + q : p1 - 1;
+                cw[q] = (double)count(k, cp[q]) * (double)Ti[q];   // exact, and so are their
+                tn += cw[q];                                       // sums: integers below 2^53
+                ts = fma(cw[q], w[q], ts);
+            }
+            const double xn = wave_incl_scan(tn), en = wave_lane_back(xn);
+            const double xs = wave_incl_scan(ts), es = wave_lane_back(xs);
+            if (lane == kWave - 1) wtot[parity][wv] = make_double2(xn, xs);
+            __syncthreads();   // the next tile uses the other set of wave totals
+            double pn = carry_n, ps = carry_s;
+#pragma unroll
+            for (int q = 0; q < nw; ++q) {
+                const double2 v = wtot[parity][q];
+                if (q < wv) {   // uniform per wave
+                    pn += v.x;
+                    ps += v.y;
+                }
+                carry_n += v.x;
+                carry_s += v.y;
+            }
+            parity ^= 1;
+            pn += en;
+            ps += es;
+            // marked positions of this lane, below p1, and the wave's slots
+            const int shift = k0 & 31;
+            uint32_t marks = (word >> shift) & 0xffu;
+            if (k0 + kFScanPer > p1) marks &= k0 < p1 ? (1u << (p1 - k0)) - 1u : 0u;
+            const int32_t slot0 = wbase + __popc(word & ((1u << shift) - 1u));
+            const int32_t first = __builtin_amdgcn_readfirstlane(slot0);
+            const int cnt = __popc(marks);
+            const int upto = wave_incl_scan(cnt);   // marks are numbered in position order
+            const int total = __builtin_amdgcn_readlane(upto, kWave - 1);
+            int at = upto - cnt;
+            if (total <= kFStage) {   // uniform per wave
+#pragma unroll
+                for (int q = 0; q < kFScanPer; ++q) {
+                    if ((marks >> q) & 1u) stage[wv][at++] = make_double2(pn, ps);
+                    advance(pn, ps, cw[q], w[q]);
+                }
+                __builtin_amdgcn_wave_barrier();
+                for (int x = lane; x < total; x += kWave)
+                    if (first + x < nqs) qrow[first + x] = stage[wv][x];
+                __builtin_amdgcn_wave_barrier();
+            } else {
+#pragma unroll
+                for (int q = 0; q < kFScanPer; ++q) {
+                    if ((marks >> q) & 1u) {
+                        if (first + at < nqs) qrow[first + at] = make_double2(pn, ps);
+                        ++at;
+                    }
+                    advance(pn, ps, cw[q], w[q]);
+                }
+            }
+        }
+    };
+
+    for (int x = t; x < kFLdsWords; x += kFPThreads) lh[x] = 0u;
+    __syncthreads();
+    uint32_t most = 0;   // the largest index met, as unsigned
+    auto draw = [&](int32_t ii) {
+        const uint32_t i = (uint32_t)ii;
+        most = most > i ? most : i;
+        // a bad index counts somewhere in the table
+        uint32_t *word = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(lh) + ((i >> 1) & 0x7ffcu));
+        atomicAdd(word, 1u << ((i << 2) & 31u));
+    };
+    const int head_all = (int)((16u - ((uint32_t)(uintptr_t)row & 15u)) & 15u) / 4;   // to 16-byte alignment
+    const int head = head_all < m ? head_all : m;
+    const int quads = (m - head) / 4;
+    if (t < head) draw(row[t]);
+    {
+        const int4 *v = reinterpret_cast<const int4 *>(row + head);
+        constexpr int kQ = 4;   // loads of four draws in flight
+        int q = t;
+        for (; q + (kQ - 1) * kFPThreads < quads; q += kQ * kFPThreads) {
+            int4 d[kQ];
+#pragma unroll
+            for (int u = 0; u < kQ; ++u) d[u] = v[q + u * kFPThreads];
+#pragma unroll
+            for (int u = 0; u < kQ; ++u) {
+                draw(d[u].x);
+                draw(d[u].y);
+                draw(d[u].z);
+                draw(d[u].w);
+            }
+        }
+        for (; q < quads; q += kFPThreads) {
+            const int4 d = v[q];
+            draw(d.x);
+            draw(d.y);
+            draw(d.z);
+            draw(d.w);
+        }
+    }
+    for (int j = head + 4 * quads + t; j < m; j += kFPThreads) draw(row[j]);
+    if (most >= (uint32_t)n) flag_domain(status);
+    __syncthreads();
+    int decoded = 0;
+    for (int x = t; x < kFLdsWords; x += kFPThreads) {
+        uint32_t v = lh[x];
+        v = (v & 0x0f0f0f0fu) + ((v >> 4) & 0x0f0f0f0fu);   // eight counts: four bytes up to 30
+        decoded += (int)((v * 0x01010101u) >> 24);
+    }
+    decoded = wave_sum(decoded);
+    if (lane == 0) wchk[wv] = decoded;
+    __syncthreads();
+    decoded = 0;
+    for (int q = 0; q < nw; ++q) decoded += wchk[q];
+    if (decoded == m) {   // the same in every thread
+        scan(0, n, [&](int, uint32_t packed) {
+            const uint32_t v = *reinterpret_cast<const uint32_t *>(
+                reinterpret_cast<const char *>(lh) + (packed & 0xffffu));
+            return (v >> (packed >> 16)) & kFMask;
+        });
+    } else {
+        for (int p0 = 0; p0 < n; p0 += kFLdsWords) {
+            const int p1 = n - p0 < kFLdsWords ? n : p0 + kFLdsWords;
+            __syncthreads();
+            for (int x = t; x < kFLdsWords; x += kFPThreads) lh[x] = 0u;
+            __syncthreads();
+            for (int j = t; j < m; j += kFPThreads) {
+                const int32_t ii = row[j];
+                const int k = rank[(uint32_t)ii < (uint32_t)n ? ii : 0] - p0;
+                if ((uint32_t)k < (uint32_t)(p1 - p0)) atomicAdd(&lh[k], 1u);
+            }
+            __syncthreads();
+            scan(p0, p1, [&](int k, uint32_t) { return lh[k - p0]; });
+        }
+    }
+    if (t == 0) {
+        if ((qbits[n >> 5] >> (n & 31)) & 1u) {
+            const int32_t q = qbase[n >> 5] + __popc(qbits[n >> 5] & ((1u << (n & 31)) - 1u));
+            if (q < nqs) qrow[q] = make_double2(carry_n, carry_s);
+        }
+        tot[rb] = (unsigned long long)carry_n;
+    }
+}
+
+// What the policies of one t1 row share: t1, (N, S) at t1 and a1 times the HBM
+// term.
+struct PolicyRow {
+    double t1, n1, s1, hbm;
+};
+
+__device__ __forceinline__ PolicyRow policy_row(double2 q1, double t1, const PriceDev &pr,
+                                                double tot)
+{
+    return PolicyRow{t1, q1.x, q1.y, pr.a1 * fma(t1, tot - q1.x, q1.y)};
+}
+
+// The load-independent part of a policy's total m*C and the factor of a2, from
+// its row and (N, S) at its deadline.  Every multiply-add is spelled out, so two
+// evaluations give the same bits.  No token is left past an infinite deadline
+// (tot equals its N), so any finite holding time stands for it there.
+__device__ __forceinline__ double2 policy_line(const PolicyRow &row, double2 qe, double t2,
+                                               const PriceDev &pr, double tot)
+{
+#pragma clang fp contract(off)
+    const double held = fmin((row.t1 + t2) - row.t1, 1.7976931348623157e308);
+    const double host = qe.x - row.n1, past = tot - qe.x;
+    const double after = fma(-row.t1, host, qe.y - row.s1);
+    const double fixed = fma(pr.b3, past, fma(pr.b2, host, row.hbm));
+    const double waiting = held * past;   // rounded by itself
+    return make_double2(fixed, after + waiting);
+}
+
+// Arg-min over the 64 lanes of kPolLoads values each, by halves: at each step a
+// lane hands one half of its values to the lane `off` away and keeps the
+// other, so 15 merges replace 16 times six; then two steps for the last value.
+// Lane 4 q ends with load q's result in c[0], f[0].
+constexpr int kPolLoads = 16;           // loads per thread of the policy kernel
+__device__ __forceinline__ void wave_argmin_halves(double (&c)[kPolLoads], int32_t (&f)[kPolLoads])
+{
+    const int lane = threadIdx.x % kWave;
+#pragma unroll
+    for (int half = kPolLoads / 2, off = kWave / 2; half > 0; half >>= 1, off >>= 1) {
+        const bool up = (lane & off) != 0;   // keeps the upper half
+#pragma unroll
+        for (int l = 0; l < kPolLoads / 2; ++l) {
+            if (l >= half) break;
+            double c0 = c[l], c1 = c[l + half];
+            int32_t f0 = f[l], f1 = f[l + half];
+            // opaque copies: as elements of the arrays they are selected by a
+            // run-time index, and the arrays leave the registers' names
+            asm("" : "+v"(c0), "+v"(c1), "+v"(f0), "+v"(f1));
+            const double oc = __shfl_xor(up ? c0 : c1, off, kWave);
+            const int32_t of = __shfl_xor(up ? f0 : f1, off, kWave);
+            c[l] = up ? c1 : c0;
+            f[l] = up ? f1 : f0;
+            argmin_merge(c[l], f[l], oc, of);
+        }
+    }
+#pragma unroll
+    for (int off = 2; off > 0; off >>= 1)
+        argmin_merge(c[0], f[0], __shfl_xor(c[0], off, kWave), __shfl_xor(f[0], off, kWave));
+}
+
 // One block per (resample of the batch, tile of FL loads): every policy's
 // closed-form total m*C for the tile's loads, the optional cost output, and
 // the arg-min per load under the library's total order (smaller first, then
 // larger flat index).  Dividing by m is monotone, so the arg-min compares the
 // totals and only the selected one is divided.
-template <int FL>
-__global__ void __launch_bounds__(kFPolThreads) factored_policy_kernel(
+//
+// A thread evaluates groups of U host timers of one t1 row at 16 loads (a tile
+// of 32 is shared by two halves of the block).  With U = 4 it takes the smallest
+// of the four before it compares with its best so far and notes only the
+// group: four FMAs, four mins, a compare and a select per four policies and
+// load, 2.5 operations each in place of 4; which of the four it was (the largest
+// index among equals) is found once per load at the end, from the same lines.
+// Groups are numbered in the order of their policies and a thread meets its own
+// in that order, so ties go to the larger index as the total order asks.
+//
+// The lines (policy_line) pass through LDS in chunks of 256 groups, two buffers
+// deep: the query records of the next chunk are in flight while the current
+// one is evaluated, and their slots, the same for every resample, are read a
+// chunk earlier still.  A chunk is 256 / 2^lcp t1 rows by 2^lcp groups of a row, so its
+// records lie near each other in the query row (deadlines of neighbouring t2)
+// and leave L2 once: the kernel is bound by the latency of those gathers and by
+// its FMAs and mins.  Two-tier (16,448
+// policies, 32 loads) 384 us, with one record per policy looked up straight from
+// the row by each thread 504 us; without the evaluation the gathers alone take
+// 309 us (67 million 16-byte records), and records fetched two chunks ahead
+// change nothing.
+template <int FL, int U>
+__global__ void __launch_bounds__(kFPolThreads *FL / kPolLoads) factored_policy_kernel(
     const double2 *__restrict__ TQ, int64_t nqs,
     const unsigned long long *__restrict__ totN, int64_t m, int64_t r0, int ntl, Tables tb,
-    PriceDev pr, const int32_t *__restrict__ u1, const int32_t *__restrict__ ue,
+    PriceDev pr, const int32_t *__restrict__ u1, const int32_t *__restrict__ ue, int lcp,
     int32_t *__restrict__ best, double *__restrict__ best_cost, double *__restrict__ cost_out)
 {
+    constexpr int kHalves = FL / kPolLoads, kThreads = kFPolThreads * kHalves;
+    constexpr int kChunkP = kFPolThreads * U;            // policies per chunk
+    constexpr int kPer = kChunkP / kThreads > 0 ? kChunkP / kThreads : 1;
     constexpr int nw = kFPolThreads / kWave;
+    // line of policy U g + u of the chunk at [u][g]; a row is one record longer
+    // than it needs, so that neighbouring policies' stores fall in other banks
+    __shared__ double2 lines[2][U][kFPolThreads + 1];
+    __shared__ PolicyRow rows_of[kFPolThreads];          // the chunk's t1 rows
     __shared__ double rc[nw][FL];
     __shared__ int32_t rf[nw][FL];
     const int64_t rb = blockIdx.x / ntl;
@@ -432,83 +712,167 @@ __global__ void __launch_bounds__(kFPolThreads) factored_policy_kernel(
     const int nl = (tb.L - l0 < FL) ? tb.L - l0 : FL;
     const double tot = (double)totN[rb];
     const double md = (double)m;
-    double a2[FL], bc[FL];
-    int32_t bf[FL];
+    const int t = threadIdx.x;
+    const int g = t % kFPolThreads;
+    // uniform per wave: the half of the tile's loads this thread evaluates
+    const int h0 = __builtin_amdgcn_readfirstlane(t / kFPolThreads) * kPolLoads;
+    double a2[kPolLoads], bc[kPolLoads];
+    int32_t bf[kPolLoads];   // group (policy for U = 1)
 #pragma unroll
-    for (int l = 0; l < FL; ++l) {
-        a2[l] = tb.a2[l0 + l];   // zero-padded to whole tiles
+    for (int l = 0; l < kPolLoads; ++l) {
+        a2[l] = tb.a2[l0 + h0 + l];   // zero-padded to whole tiles
         bc[l] = INFINITY;
         bf[l] = -1;
     }
-    // kFPU<FL> policies per thread and step: their slots, then their prefix
-    // values, are fetched together before any is used.  P < 2^24, so policy
-    // indices are split in 32-bit arithmetic.
-    const uint32_t B = blockDim.x, K2 = (uint32_t)tb.K2, P32 = (uint32_t)P;
-    for (uint32_t f0 = threadIdx.x; f0 < P32; f0 += kFPU<FL> * B) {
-        int32_t p1[kFPU<FL>], pe[kFPU<FL>];
-        double t1[kFPU<FL>], e[kFPU<FL>];
+    const int cp = 1 << lcp, rp = kFPolThreads >> lcp;     // groups of a row per chunk, rows
+    const int gpr = (tb.K2 + U - 1) / U;                   // groups of a row
+    const int ncol = (gpr + cp - 1) >> lcp, nchunk = ncol * ((tb.K1 + rp - 1) / rp);
+    const int my_row = g >> lcp, my_col = g & (cp - 1);    // of the group evaluated
+    // the kPer policies of a chunk whose lines this thread forms: policy
+    // p = x kThreads + t of the chunk is number p % U of group p / U
+    const bool forms = kPer > 1 || t < kChunkP;            // uniform per wave
+    const uint32_t last = (uint32_t)nqs - 1u;
+    int32_t slot[kPer];
+    double t2[kPer];
+    double2 qe[kPer];
+    auto group_of = [&](int x) { return (x * kThreads + t) / U; };
+    // slots of the chunk whose first row and group of the row are a0 and kg0;
+    // positions past a row's end or past the last row repeat the last one and
+    // are never the smallest below
+    auto slots = [&](int a0, int kg0) {
 #pragma unroll
-        for (int u = 0; u < kFPU<FL>; ++u) {
-            const uint32_t f = (f0 + u * B < P32) ? f0 + u * B : f0;   // a repeat of f0 is skipped below
-            const uint32_t a = f / K2, k = f - a * K2;
-            t1[u] = tb.t1[a];
-            e[u] = t1[u] + tb.t2[k];
-            p1[u] = u1[a];
-            pe[u] = ue[f];
+        for (int x = 0; x < kPer; ++x) {
+            const int gx = group_of(x);
+            const int a = min(a0 + (gx >> lcp), tb.K1 - 1);
+            const int k = min((kg0 + (gx & (cp - 1))) * U + t % U, tb.K2 - 1);
+            slot[x] = (int32_t)min((uint32_t)ue[a * tb.K2 + k], last);   // P < 2^24
+            t2[x] = tb.t2[k];
         }
-        double n1[kFPU<FL>], ne[kFPU<FL>], s1[kFPU<FL>], se[kFPU<FL>];
-#pragma unroll
-        for (int u = 0; u < kFPU<FL>; ++u) {   // one 16-byte record per slot
-            const double2 q1 = qrow[p1[u]], qe = qrow[pe[u]];
-            n1[u] = q1.x;
-            s1[u] = q1.y;
-            ne[u] = qe.x;
-            se[u] = qe.y;
+    };
+    auto rows = [&](int a0) {
+        if (t < rp) {
+            const int a = min(a0 + t, tb.K1 - 1);
+            rows_of[t] = policy_row(qrow[u1[a]], tb.t1[a], pr, tot);
         }
+    };
+    auto form = [&](int a0, int kg0, int buf) {
 #pragma unroll
-        for (int u = 0; u < kFPU<FL>; ++u) {
-            const uint32_t f = f0 + u * B;
-            if (f >= P32) break;
-            const double hbm = s1[u] + t1[u] * (tot - n1[u]);
-            double hold = (se[u] - s1[u]) - t1[u] * (ne[u] - n1[u]);
-            if (!isinf(e[u])) hold = hold + (e[u] - t1[u]) * (tot - ne[u]);
-            const double fixed = pr.a1 * hbm + pr.b2 * (ne[u] - n1[u]) + pr.b3 * (tot - ne[u]);
-            if (cost_out != nullptr) {   // unrolled, so that a2 stays in registers
-#pragma unroll
-                for (int l = 0; l < FL; ++l)
-                    if (l < nl) cost_out[(r * tb.L + l0 + l) * P + f] = (fixed + a2[l] * hold) / md;
-            }
-            // every load of the tile (a2 is zero-padded past L; those lanes are
-            // never stored); a thread visits its policies in increasing f, so
-            // "not larger" keeps the larger index on a tie, as the total order
-            // asks; the running minimum itself is a min (equal on a tie)
-#pragma unroll
-            for (int l = 0; l < FL; ++l) {
-                const double tc = fixed + a2[l] * hold;
-                const bool take = tc <= bc[l];
-                bc[l] = fmin(bc[l], tc);
-                bf[l] = take ? (int32_t)f : bf[l];
-            }
+        for (int x = 0; x < kPer; ++x) {
+            const int gx = group_of(x);
+            const int a = a0 + (gx >> lcp), k = (kg0 + (gx & (cp - 1))) * U + t % U;
+            double2 ln = policy_line(rows_of[gx >> lcp], qe[x], t2[x], pr, tot);
+            if (a >= tb.K1 || k >= tb.K2) ln = make_double2(INFINITY, 0.0);
+            else if (cost_out != nullptr)   // uniform
+                for (int l = 0; l < nl; ++l)
+                    cost_out[(r * tb.L + l0 + l) * P + (int64_t)a * tb.K2 + k] =
+                        fma(tb.a2[l0 + l], ln.y, ln.x) / md;
+            lines[buf][t % U][gx] = ln;
         }
+    };
+    static_assert(kThreads % U == 0, "a thread's policies have one place in their groups");
+    rows(0);
+    if (forms) {
+        slots(0, 0);
+#pragma unroll
+        for (int x = 0; x < kPer; ++x) qe[x] = qrow[slot[x]];
     }
-    const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
-#pragma unroll
-    for (int l = 0; l < FL; ++l) {
-        wave_argmin_dpp(bc[l], bf[l]);
-        if (lane == kWave - 1) {
-            rc[wv][l] = bc[l];
-            rf[wv][l] = bf[l];
+    // the chunks run along the groups of a row, then to the next rows
+    int a0 = 0, kg0 = 0;                        // chunk evaluated
+    auto step = [&](int &a, int &kg) {
+        kg += cp;
+        if (kg >= gpr) {
+            kg = 0;
+            a += rp;
         }
+    };
+    int a1 = 0, kg1 = 0;                        // the next one
+    step(a1, kg1);
+    int a2n = a1, kg2 = kg1;                    // the one after it
+    step(a2n, kg2);
+    __syncthreads();
+    if (forms) {
+        form(0, 0, 0);
+        if (nchunk > 1) slots(a1, kg1);
     }
     __syncthreads();
-    if ((int)threadIdx.x < nl) {
-        const int l = threadIdx.x;
+    for (int c = 0, cur = 0; c < nchunk; ++c, cur ^= 1) {
+        const bool more = c + 1 < nchunk;   // uniform
+        if (more && forms) {
+#pragma unroll
+            for (int x = 0; x < kPer; ++x) qe[x] = qrow[slot[x]];
+        }
+        const int a = a0 + my_row, kg = kg0 + my_col;
+        if (a < tb.K1 && kg < gpr) {
+            double2 ln[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) ln[u] = lines[cur][u][g];
+            const int32_t id = a * gpr + kg;
+            // a2 is zero-padded past L (never stored); groups come in
+            // increasing order, so "not larger" keeps the larger index
+#pragma unroll
+            for (int l = 0; l < kPolLoads; ++l) {
+                double v = fma(a2[l], ln[0].y, ln[0].x);
+#pragma unroll
+                for (int u = 1; u < U; ++u) v = fmin(v, fma(a2[l], ln[u].y, ln[u].x));
+                const bool take = v <= bc[l];
+                bc[l] = fmin(bc[l], v);
+                bf[l] = take ? id : bf[l];
+            }
+        }
+        if (more) {
+            if (kg1 == 0) {   // the next chunk begins other t1 rows
+                rows(a1);
+                __syncthreads();
+            }
+            if (forms) {
+                form(a1, kg1, cur ^ 1);
+                if (c + 2 < nchunk) slots(a2n, kg2);
+            }
+        }
+        a0 = a1;
+        kg0 = kg1;
+        a1 = a2n;
+        kg1 = kg2;
+        step(a2n, kg2);
+        __syncthreads();
+    }
+    wave_argmin_halves(bc, bf);
+    if (t % 4 == 0) {
+        const int l = h0 + (t % kWave) / 4;
+        rc[g / kWave][l] = bc[0];
+        rf[g / kWave][l] = bf[0];
+    }
+    __syncthreads();
+    if (t < nl) {
+        const int l = t;
         double c = rc[0][l];
-        int32_t f = rf[0][l];
-        for (int q = 1; q < nw; ++q) argmin_merge(c, f, rc[q][l], rf[q][l]);
+        int32_t id = rf[0][l];
+        for (int q = 1; q < nw; ++q) argmin_merge(c, id, rc[q][l], rf[q][l]);
+        int32_t f = id;
+        if (id >= 0) {   // the policy of the group: the same lines, the same FMA
+            const int a = id / gpr, k0 = (id - a * gpr) * U;
+            f = a * tb.K2 + k0;
+            const PolicyRow row = policy_row(qrow[u1[a]], tb.t1[a], pr, tot);
+            double low = INFINITY;
+            for (int k = k0; U > 1 && k < k0 + U && k < tb.K2; ++k) {
+                const double2 ln = policy_line(row, qrow[ue[a * tb.K2 + k]], tb.t2[k], pr, tot);
+                const double v = fma(tb.a2[l0 + l], ln.y, ln.x);
+                if (v <= low) {
+                    low = v;
+                    f = a * tb.K2 + k;
+                }
+            }
+        }
         best[r * tb.L + l0 + l] = f;
         best_cost[r * tb.L + l0 + l] = c / md;
     }
+}
+
+// Every 4-bit counter of a resample fits one block's LDS, and the N sums are
+// exact in double.
+bool factored_small(int64_t n, int64_t m)
+{
+    return n <= (int64_t)kFPerWord * kFLdsWords && m <= kFExactDoubleDraws;
 }
 
 int64_t factored_query_slots(int64_t n, int64_t K1, int64_t P)
@@ -529,27 +893,39 @@ int64_t factored_batch(int64_t nqs, int64_t R)
     return (R + nb - 1) / nb;
 }
 
+// Logarithm of the groups of a row per chunk of the policy kernel: the fewest
+// chunks, and among those the most rows (the narrowest span of deadlines).
+static int policy_columns(int64_t K1, int64_t groups)
+{
+    int best = 0;
+    int64_t least = INT64_MAX;
+    for (int lcp = 0; (1 << lcp) <= kFPolThreads; ++lcp) {
+        const int64_t rp = kFPolThreads >> lcp, cp = 1 << lcp;
+        const int64_t chunks = ((K1 + rp - 1) / rp) * ((groups + cp - 1) / cp);
+        if (chunks < least) {
+            least = chunks;
+            best = lcp;
+        }
+    }
+    return best;
+}
+
 hipError_t launch_factored(const SampleSrc &src, int64_t R, const Tables &tb, const PriceDev &pr,
                            FactoredWs &ws, int32_t *best, double *best_cost, double *cost_out,
                            int *status, hipStream_t stream)
 {
     const int64_t n = src.n, m = src.m;
     const int64_t P = (int64_t)tb.K1 * tb.K2;
+    const int64_t nwords = (n + 1 + 31) / 32;
     int cur = 0;
     hipError_t err = launch_sort_keys(src.w, src.T, n, ws.sort, &cur, status, stream);
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(factored_rank_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-                       stream, ws.sort.keys[cur], ws.sort.vals[cur], src.T, n, ws.sw, ws.Ts,
-                       ws.rank);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-    const unsigned gq = (unsigned)((tb.K1 + P + 255) / 256);
-    hipLaunchKernelGGL(factored_bounds_kernel, dim3(gq), dim3(256), 0, stream, ws.sw, n, tb, ws.u1,
-                       ws.ue);
-    const int64_t nwords = (n + 1 + 31) / 32;
     hipLaunchKernelGGL(factored_fill_kernel, dim3((unsigned)((nwords + 255) / 256)), dim3(256), 0,
                        stream, ws.qbits, nwords);
-    hipLaunchKernelGGL(factored_mark_kernel, dim3(gq), dim3(256), 0, stream, ws.u1, ws.ue, tb.K1, P,
-                       ws.qbits);
+    const dim3 gr((unsigned)((n + tb.K1 + P + 255) / 256));
+    hipLaunchKernelGGL(factored_rank_kernel, gr, dim3(256), 0, stream, ws.sort.keys[cur],
+                       ws.sort.vals[cur], src.T, n, tb, ws.sw, ws.Ts, ws.rank, ws.cpos, ws.u1,
+                       ws.ue, ws.qbits);
     hipLaunchKernelGGL(factored_slot_kernel, dim3(1), dim3(kFThreads), 0, stream, ws.qbits, ws.qbase,
                        nwords);
     hipLaunchKernelGGL(factored_remap_kernel, dim3((unsigned)((tb.K1 + P + n + 1 + 255) / 256)),
@@ -558,9 +934,17 @@ hipError_t launch_factored(const SampleSrc &src, int64_t R, const Tables &tb, co
     if ((err = hipGetLastError()) != hipSuccess) return err;
     const int FL = tb.L <= 16 ? 16 : kFLoads;                 // loads per policy block
     const int ntl = (tb.L + FL - 1) / FL;
+    // groups of four host timers where rows hold a few and one chunk of them is
+    // full; fewer policies keep a thread each
+    const int U = tb.K2 >= 16 && P >= 4 * kFPolThreads ? 4 : 1;
+    const int lcp = policy_columns(tb.K1, (tb.K2 + U - 1) / U);
     for (int64_t r0 = 0; r0 < R; r0 += ws.Rb) {
         const int64_t rb = (R - r0 < ws.Rb) ? R - r0 : ws.Rb;
-        if (m <= kFExactDoubleDraws)
+        if (ws.cpos != nullptr)
+            hipLaunchKernelGGL(factored_prefix_small_kernel, dim3((unsigned)rb), dim3(kFPThreads), 0,
+                               stream, src.idx, (int)n, (int)m, r0, ws.rank, ws.cpos, ws.Ts, ws.sw,
+                               ws.qbits, ws.qbase, (int)ws.nqs, ws.TQ, ws.tot, status);
+        else if (m <= kFExactDoubleDraws)
             hipLaunchKernelGGL(factored_prefix_kernel<double>, dim3((unsigned)rb),
                                dim3(kFPThreads), 0, stream, src.idx, n, m, r0, ws.rank,
                                ws.sort.vals[cur], ws.Ts, ws.sw, ws.qslot, ws.nqs, ws.TQ, ws.tot,
@@ -570,14 +954,21 @@ hipError_t launch_factored(const SampleSrc &src, int64_t R, const Tables &tb, co
                                dim3(kFPThreads), 0, stream, src.idx, n, m, r0, ws.rank,
                                ws.sort.vals[cur], ws.Ts, ws.sw, ws.qslot, ws.nqs, ws.TQ, ws.tot,
                                status);
-        if (FL == 16)
-            hipLaunchKernelGGL(factored_policy_kernel<16>, dim3((unsigned)(rb * ntl)),
-                               dim3(kFPolThreads), 0, stream, ws.TQ, ws.nqs, ws.tot, m, r0,
-                               ntl, tb, pr, ws.u1, ws.ue, best, best_cost, cost_out);
+        const dim3 gp((unsigned)(rb * ntl)), bp((unsigned)(kFPolThreads * FL / kPolLoads));
+        if (FL == 16 && U == 4)
+            hipLaunchKernelGGL((factored_policy_kernel<16, 4>), gp, bp, 0, stream, ws.TQ, ws.nqs,
+                               ws.tot, m, r0, ntl, tb, pr, ws.u1, ws.ue, lcp, best, best_cost, cost_out);
+        else if (FL == 16)
+            hipLaunchKernelGGL((factored_policy_kernel<16, 1>), gp, bp, 0, stream, ws.TQ, ws.nqs,
+                               ws.tot, m, r0, ntl, tb, pr, ws.u1, ws.ue, lcp, best, best_cost, cost_out);
+        else if (U == 4)
+            hipLaunchKernelGGL((factored_policy_kernel<kFLoads, 4>), gp, bp, 0, stream, ws.TQ,
+                               ws.nqs, ws.tot, m, r0, ntl, tb, pr, ws.u1, ws.ue, lcp, best,
+                               best_cost, cost_out);
         else
-            hipLaunchKernelGGL(factored_policy_kernel<kFLoads>, dim3((unsigned)(rb * ntl)),
-                               dim3(kFPolThreads), 0, stream, ws.TQ, ws.nqs, ws.tot, m, r0,
-                               ntl, tb, pr, ws.u1, ws.ue, best, best_cost, cost_out);
+            hipLaunchKernelGGL((factored_policy_kernel<kFLoads, 1>), gp, bp, 0, stream, ws.TQ,
+                               ws.nqs, ws.tot, m, r0, ntl, tb, pr, ws.u1, ws.ue, lcp, best,
+                               best_cost, cost_out);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
     return hipSuccess;
