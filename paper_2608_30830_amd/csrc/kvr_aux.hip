@@ -15,16 +15,11 @@ __global__ void clear_status_kernel(int *status)
 }
 
 constexpr int kUploadMax = 384;
+// Host tables travel as kernel arguments, so the caller's host buffers are
+// captured at launch and no pinned staging or host synchronisation is needed.
 struct UploadPayload {
     double v[kUploadMax];
 };
-
-// Host tables travel as kernel arguments, so the caller's host buffers are
-// captured at launch and no pinned staging or host synchronisation is needed.
-__global__ void upload_kernel(double *dst, int n, UploadPayload p)
-{
-    for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i] = p.v[i];
-}
 
 hipError_t launch_clear_status(int *status, hipStream_t stream)
 {
@@ -43,60 +38,65 @@ hipError_t launch_export_status(const int *status, int32_t *out, hipStream_t str
     return hipGetLastError();
 }
 
-// Clears the status word and a range of counters, and stores up to three host
-// tables in one launch when they fit one payload together.
+// Clears the status word and a range of counters (the first launch), and stores
+// the part of up to three host tables, one after another, that begins at `from`.
 struct StagePlan {
     double *dst[3];
-    int cnt[3];
+    int64_t cnt[3];
+    int64_t from;
+    int n;               // values in the payload
+    int *status;         // nullptr after the first launch
     unsigned *zero;
     int nzero;
 };
 
-__global__ void stage_kernel(int *status, StagePlan sp, UploadPayload p)
+__global__ void stage_kernel(StagePlan sp, UploadPayload p)
 {
-    if (threadIdx.x == 0) status[0] = 0;
-    for (int i = threadIdx.x; i < sp.nzero; i += blockDim.x) sp.zero[i] = 0u;
-    int off = 0;
-    for (int t = 0; t < 3; ++t) {
-        for (int i = threadIdx.x; i < sp.cnt[t]; i += blockDim.x) sp.dst[t][i] = p.v[off + i];
-        off += sp.cnt[t];
+    if (sp.status != nullptr) {
+        if (threadIdx.x == 0) sp.status[0] = 0;
+        for (int i = threadIdx.x; i < sp.nzero; i += blockDim.x) sp.zero[i] = 0u;
+    }
+    for (int i = threadIdx.x; i < sp.n; i += blockDim.x) {
+        int64_t g = sp.from + i;
+        int t = 0;
+        while (t < 2 && g >= sp.cnt[t]) g -= sp.cnt[t++];
+        sp.dst[t][g] = p.v[i];
     }
 }
 
 hipError_t launch_stage(int *status, double *const dst[3], const double *const src[3],
                         const int64_t cnt[3], unsigned *zero, int nzero, hipStream_t stream)
 {
-    const bool one = cnt[0] + cnt[1] + cnt[2] <= kUploadMax;
     StagePlan sp;
-    UploadPayload p;
+    for (int t = 0; t < 3; ++t) {
+        sp.dst[t] = dst[t];
+        sp.cnt[t] = cnt[t];
+    }
+    sp.status = status;
     sp.zero = zero;
     sp.nzero = zero != nullptr ? nzero : 0;
-    int off = 0;
-    for (int t = 0; t < 3; ++t) {   // the tables ride along when they fit, else follow
-        sp.dst[t] = dst[t];
-        sp.cnt[t] = one ? (int)cnt[t] : 0;
-        for (int64_t i = 0; i < sp.cnt[t]; ++i) p.v[off++] = src[t][i];
-    }
-    for (int i = off; i < kUploadMax; ++i) p.v[i] = 0.0;
-    hipLaunchKernelGGL(stage_kernel, dim3(1), dim3(256), 0, stream, status, sp, p);
-    hipError_t err = hipGetLastError();
-    for (int t = 0; t < 3 && !one && err == hipSuccess; ++t)
-        err = launch_upload(dst[t], src[t], cnt[t], stream);
-    return err;
-}
-
-hipError_t launch_upload(double *dst, const double *host_src, int64_t count, hipStream_t stream)
-{
-    for (int64_t off = 0; off < count; off += kUploadMax) {
-        int c = (int)((count - off) < kUploadMax ? (count - off) : kUploadMax);
+    sp.from = 0;
+    const int64_t all = cnt[0] + cnt[1] + cnt[2];
+    int t = 0;
+    int64_t at = 0;      // next value: src[t][at]
+    hipError_t err = hipSuccess;
+    do {                 // a launch per payload, the tables packed across them
         UploadPayload p;
-        for (int i = 0; i < c; ++i) p.v[i] = host_src[off + i];
-        for (int i = c; i < kUploadMax; ++i) p.v[i] = 0.0;
-        hipLaunchKernelGGL(upload_kernel, dim3(1), dim3(256), 0, stream, dst + off, c, p);
-        hipError_t err = hipGetLastError();
-        if (err != hipSuccess) return err;
-    }
-    return hipSuccess;
+        sp.n = 0;
+        for (; sp.n < kUploadMax && sp.from + sp.n < all; ++sp.n) {
+            while (at >= cnt[t]) {
+                ++t;
+                at = 0;
+            }
+            p.v[sp.n] = src[t][at++];
+        }
+        for (int i = sp.n; i < kUploadMax; ++i) p.v[i] = 0.0;
+        hipLaunchKernelGGL(stage_kernel, dim3(1), dim3(256), 0, stream, sp, p);
+        err = hipGetLastError();
+        sp.from += sp.n;
+        sp.status = nullptr;
+    } while (err == hipSuccess && sp.from < all);
+    return err;
 }
 
 // ------------------------------------------------------------------- X, G --

@@ -26,18 +26,22 @@
 #include "kvr_device.h"
 #include "kvr_dpp.h"
 
+#include <math.h>
+
 namespace kvr {
 
 constexpr int kBinThreads = 1024;
 constexpr int kBinIlp = 4;                 // waits per thread in flight
 constexpr int kBinRange = 4095;            // bins of one range: 128 KiB of LDS with their edges
 constexpr int64_t kBinChunk = 65536;       // waits per block at most: 48-bit limbs, 64-bit sums
-constexpr int64_t kBinBlocks = 512;        // blocks that fill the chip (two to a CU)
+constexpr int64_t kBinBlocks = 512;        // chunks that fill the chip (two blocks to a CU)
 constexpr int kBinFused = 4096;            // bins that the closed form's own blocks scan
-constexpr int kBinWords = 4;               // per bin: sum of T, then three 32-bit limbs of S
+constexpr int kBinWords = 4;               // per bin: sum of T, then three 47-bit limbs of S
+constexpr uint64_t kLimb = (uint64_t(1) << 47) - 1;
 constexpr int kBinCopies = 8;              // of every bin, while a block scans them all itself
 constexpr int kFixedEdges = 211;           // 2^-1070, 2^-1060, ..., 2^1020, the largest finite
 constexpr int kBuckets = 512;              // search table: 16 buckets per binade, 32 binades
+constexpr int kBinTiles = 64;              // tiles of kBinThreads bins, of 2 * 16,384 + 212 at most
 constexpr int kBinLdsTable = 4096;         // timer-table entries staged in LDS
 constexpr int kItemLanes = 8;              // lanes per threshold
 constexpr int kFormPolicies = 64;          // policies of one closed-form block
@@ -45,29 +49,31 @@ constexpr int kFormPolicies = 64;          // policies of one closed-form block
 static inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Waits per block: about one block per CU before a thread takes a second wait,
-// two blocks per CU for large samples, never more than kBinChunk.
-static int64_t bin_chunk(int64_t n)
+// Waits per chunk, never more than kBinChunk.  B chunks cost n / B waits of work
+// each (0.6 us per 1,024) and B * bins global adds of three words (about 32 a
+// nanosecond on MI355X), least together at B = sqrt(6.25 n / bins); at most two
+// blocks per CU.  (2^20 waits and 1,026 thresholds: 256 chunks
+// 55 us, the 72 of this rule 23.)
+static int64_t bin_chunk(int64_t n, int64_t bins)
 {
-    int64_t per = cdiv(n, kBinThreads * (kBinBlocks / 2));
-    if (per > 4) per = cdiv(n, kBinThreads * kBinBlocks);
-    const int64_t c = per * kBinThreads;
+    int64_t b = (int64_t)sqrt(6.25 * (double)n / (double)bins);
+    b = b < 1 ? 1 : b < kBinBlocks ? b : kBinBlocks;
+    const int64_t c = cdiv(cdiv(n, b), kBinThreads) * kBinThreads;
     return c < kBinChunk ? c : kBinChunk;
 }
 
-// Policies up to which the bins replace the sort: nine ranges of bins at most,
-// each of which reads the sample once.
+// Policies up to which the bins replace the sort: nine ranges of bins at most, each of which
+// reads the sample once.
 bool bins_apply(int64_t P) { return P <= 16384; }
 
 // Global copies of each bin, block q of the sums adding into copy q % copies:
 // with one copy the atomics of 512 blocks on the same few addresses took 28 us
 // of a 2^24-wait call with 66 thresholds (90 us; 68 with eight copies).  Reading
 // eight copies costs the closed form's blocks 5 us at 723 bins, more than the
-// adds of 98 blocks do (100,003 waits); grids of more bins spread the adds by
-// themselves.
+// adds of 98 blocks do; grids of more bins spread the adds by themselves.
 static int bin_copies(int64_t n, int64_t bins)
 {
-    return bins <= kBinFused && cdiv(n, bin_chunk(n)) > 128 ? kBinCopies : 1;
+    return bins <= kBinFused && cdiv(n, bin_chunk(n, bins)) > 128 ? kBinCopies : 1;
 }
 
 size_t bin_ws_bytes(int64_t n, int64_t K1, int64_t P)
@@ -75,7 +81,7 @@ size_t bin_ws_bytes(int64_t n, int64_t K1, int64_t P)
     const int64_t M = K1 + P + kFixedEdges;
     return align256(sizeof(double) * (M + 1)) + align256(sizeof(int32_t) * (K1 + P)) +
            align256(sizeof(uint64_t) * kBinWords * bin_copies(n, M + 1) * (M + 1)) +
-           2 * align256(sizeof(double) * (M + 1));
+           2 * align256(sizeof(double) * (M + 1 + kBinTiles));
 }
 
 void bin_ws_carve(void *base, int64_t n, int64_t K1, int64_t P, double largest, BinWs &ws)
@@ -87,7 +93,7 @@ void bin_ws_carve(void *base, int64_t n, int64_t K1, int64_t P, double largest, 
         return q;
     };
     ws.M = (int)(K1 + P) + kFixedEdges;
-    ws.chunk = bin_chunk(n);
+    ws.chunk = bin_chunk(n, ws.M + 1);
     uint64_t bits;
     __builtin_memcpy(&bits, &largest, 8);
     const int top = (int)(bits >> 48);   // largest >= 0
@@ -97,8 +103,8 @@ void bin_ws_carve(void *base, int64_t n, int64_t K1, int64_t P, double largest, 
     ws.at = (int32_t *)take(sizeof(int32_t) * (K1 + P));
     ws.copies = bin_copies(n, ws.M + 1);
     ws.bins = (unsigned long long *)take(sizeof(uint64_t) * kBinWords * ws.copies * (ws.M + 1));
-    ws.cumN = (int64_t *)take(sizeof(int64_t) * (ws.M + 1));
-    ws.cumS = (double *)take(sizeof(double) * (ws.M + 1));
+    ws.cumN = (int64_t *)take(sizeof(int64_t) * (ws.M + 1 + kBinTiles));
+    ws.cumS = (double *)take(sizeof(double) * (ws.M + 1 + kBinTiles));
 }
 
 __device__ __forceinline__ double fixed_edge(int q)
@@ -297,29 +303,32 @@ __global__ void __launch_bounds__(kBinThreads) bin_sums_kernel(const double *__r
         unsigned long long *out =
             ws.bins + ((int64_t)(b0 + q) * ws.copies + blockIdx.x % ws.copies) * kBinWords;
         atomicAdd(out, sumT[q]);
-        const uint64_t lo = lo48[q], hi = hi48[q];
-        // hi * 2^48 + lo as three 32-bit limbs (the last with the carries)
-        const uint64_t l1 = (lo >> 32) + ((hi & 0xffffu) << 16);
-        if (lo | hi) {
-            atomicAdd(out + 1, (unsigned long long)(uint32_t)lo);
-            atomicAdd(out + 2, (unsigned long long)(uint32_t)l1);
-            atomicAdd(out + 3, (unsigned long long)((hi >> 16) + (l1 >> 32)));
+        // hi48 * 2^48 + lo48 (below 2^113) as limbs of 47, 47 and 19 bits: the
+        // last is zero below 2^30 tokens a block
+        const uint64_t lo = lo48[q], hi = hi48[q] + (lo >> 48);
+        const uint64_t l0 = lo & kLimb, l1 = ((lo >> 47) & 1u) | ((hi << 1) & kLimb);
+        if (l0 | l1) {
+            atomicAdd(out + 1, l0);
+            atomicAdd(out + 2, l1);
         }
+        if (hi >> 46) atomicAdd(out + 3, hi >> 46);
     }
 }
 
-// One block of kBinThreads: the inclusive prefix sums of T and T*w over the
-// bins, each thread a run of consecutive bins, in a fixed order.  An empty
+// One block of kBinThreads: the inclusive prefix sums of T and T*w over the bins
+// [first, end), each thread a run of consecutive bins, in a fixed order
+// (cumN and cumS are indexed from first).  An empty
 // bin's S is that of the last bin before it that is not empty, bit for bit, so
 // policies that no wait separates get equal costs.
 template <typename NOut, typename SOut>
-__device__ __forceinline__ void bin_prefix(const BinWs &ws, NOut *cumN, SOut *cumS)
+__device__ __forceinline__ void bin_prefix(const BinWs &ws, int first, int end, NOut *cumN,
+                                           SOut *cumS)
 {
     __shared__ int64_t wn[kBinThreads / kWave];
     __shared__ double wsum[kBinThreads / kWave];
     __shared__ int wl[kBinThreads / kWave];
     const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
-    const int total = ws.M + 1;
+    const int total = end - first;
     const int per = (total + kBinThreads - 1) / kBinThreads;
     const int q0 = t * per, q1 = q0 + per < total ? q0 + per : total;
     auto bin_of = [&](int b, int64_t &N, double &S) {
@@ -337,21 +346,26 @@ __device__ __forceinline__ void bin_prefix(const BinWs &ws, NOut *cumN, SOut *cu
         const uint32_t e = (uint32_t)((uint64_t)__double_as_longlong(top - base) >> 52);
         const int es = (int)(e > 64u ? e : 64u);
         // the limbs count units of 2^(es - 1022 - 64)
-        const double frac = ((double)in[3] * 4294967296.0 + (double)in[2]) +
-                            (double)in[1] * 2.3283064365386963e-10;
-        S = fma(base, (double)N, ldexp(frac, es - 1022 - 32));
+        const double frac = (double)in[1] + ldexp((double)in[2] + ldexp((double)in[3], 47), 47);
+        S = fma(base, (double)N, ldexp(frac, es - 1022 - 64));
     };
+#pragma unroll 4
+    for (int b = t; b < total; b += kBinThreads) {   // coalesced, read back below
+        int64_t N;
+        double S;
+        bin_of(first + b, N, S);
+        cumN[b] = N;
+        cumS[b] = S;
+    }
+    __syncthreads();
     int64_t sn = 0;
     double ss = 0.0;
     int last = -1;
+#pragma unroll 4
     for (int b = q0; b < q1; ++b) {
-        int64_t N;
-        double S;
-        bin_of(b, N, S);
-        cumN[b] = N;   // read back below
-        cumS[b] = S;
+        const int64_t N = cumN[b];
         sn += N;
-        ss += S;
+        ss += cumS[b];
         if (N != 0) last = b;
     }
     const int64_t xn = wave_incl_scan(sn);
@@ -391,36 +405,67 @@ __device__ __forceinline__ void bin_prefix(const BinWs &ws, NOut *cumN, SOut *cu
     __syncthreads();
 }
 
+// Tile q of kBinThreads bins: the prefix sums within it, and its totals after the
+// bins' own entries.  A tile's total is the sum at its last bin, so the sum before
+// a tile is, bit for bit, the one at the last bin before it that is not empty.
 __global__ void __launch_bounds__(kBinThreads) bin_prefix_kernel(BinWs ws)
 {
-    bin_prefix(ws, ws.cumN, ws.cumS);
+    const int first = blockIdx.x * kBinThreads;
+    const int end = first + kBinThreads < ws.M + 1 ? first + kBinThreads : ws.M + 1;
+    bin_prefix(ws, first, end, ws.cumN + first, ws.cumS + first);
+    if (threadIdx.x == 0) {
+        ws.cumN[ws.M + 1 + blockIdx.x] = ws.cumN[end - 1];
+        ws.cumS[ws.M + 1 + blockIdx.x] = ws.cumS[end - 1];
+    }
 }
 
 // kFormPolicies policies per block, the block's other threads sharing their
-// loads.  FUSED: the block forms the prefix sums itself, in LDS.
+// loads.  FUSED: the block forms the prefix sums itself, in LDS; else they come
+// in tiles, whose totals every block adds up.
 template <bool FUSED>
 __global__ void __launch_bounds__(kBinThreads) bin_form_kernel(BinWs ws, int64_t n, Tables tb,
                                                                PriceDev pr,
                                                                double *__restrict__ cost)
 {
-    __shared__ int64_t lN[FUSED ? kBinFused : 1];
-    __shared__ double lS[FUSED ? kBinFused : 1];
-    const int64_t *cumN = ws.cumN;
-    const double *cumS = ws.cumS;
+    __shared__ int64_t lN[FUSED ? kBinFused : kBinTiles];
+    __shared__ double lS[FUSED ? kBinFused : kBinTiles];
     if (FUSED) {
-        bin_prefix(ws, lN, lS);
-        cumN = lN;
-        cumS = lS;
+        bin_prefix(ws, 0, ws.M + 1, lN, lS);
+    } else {
+        const int tiles = (ws.M + kBinThreads) / kBinThreads;   // of M + 1 bins
+        if ((int)threadIdx.x < tiles) {   // the sums before tile threadIdx.x
+            int64_t N = 0;
+            double S = 0.0;
+            for (int q = 0; q < (int)threadIdx.x; ++q) {
+                N += ws.cumN[ws.M + 1 + q];
+                S += ws.cumS[ws.M + 1 + q];
+            }
+            lN[threadIdx.x] = N;
+            lS[threadIdx.x] = S;
+        }
+        __syncthreads();
     }
+    auto at = [&](int b, int64_t &N, double &S) {
+        if (FUSED) {
+            N = lN[b];
+            S = lS[b];
+        } else {
+            N = lN[b / kBinThreads] + ws.cumN[b];
+            S = lS[b / kBinThreads] + ws.cumS[b];
+        }
+    };
     const int64_t P = (int64_t)tb.K1 * tb.K2;
     const int64_t f = (int64_t)blockIdx.x * kFormPolicies + threadIdx.x % kFormPolicies;
     if (f >= P) return;
     const int a = (int)(f / tb.K2), k = (int)(f % tb.K2);
     const double t1 = tb.t1[a];
-    const int u1 = ws.at[a], ue = ws.at[tb.K1 + f];
-    closed_form_values(cumN[ws.M], cumN[u1], cumN[ue], cumS[u1], cumS[ue], n, tb, pr, f, t1,
-                       t1 + tb.t2[k], (int)threadIdx.x / kFormPolicies,
-                       kBinThreads / kFormPolicies, cost);
+    int64_t tot, n1, ne;
+    double sall, s1, se;
+    at(ws.M, tot, sall);
+    at(ws.at[a], n1, s1);
+    at(ws.at[tb.K1 + f], ne, se);
+    closed_form_values(tot, n1, ne, s1, se, n, tb, pr, f, t1, t1 + tb.t2[k],
+                       (int)threadIdx.x / kFormPolicies, kBinThreads / kFormPolicies, cost);
 }
 
 hipError_t launch_binned(const double *w, const int32_t *T, int64_t n, const Tables &tb,
@@ -444,7 +489,9 @@ hipError_t launch_binned(const double *w, const int32_t *T, int64_t n, const Tab
     if (total <= kBinFused) {
         hipLaunchKernelGGL(bin_form_kernel<true>, form, block, 0, stream, ws, n, tb, pr, cost_out);
     } else {
-        hipLaunchKernelGGL(bin_prefix_kernel, dim3(1), block, 0, stream, ws);
+        const int tiles = (int)cdiv(total, kBinThreads);
+        if (tiles > kBinTiles) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(bin_prefix_kernel, dim3((unsigned)tiles), block, 0, stream, ws);
         hipLaunchKernelGGL(bin_form_kernel<false>, form, block, 0, stream, ws, n, tb, pr, cost_out);
     }
     return hipGetLastError();

@@ -97,7 +97,6 @@ int cost_grid_entry(const double *d_wait_s, const int32_t *d_ctx_tokens, int64_t
 hipError_t launch_clear_status(int *status, hipStream_t stream);
 // out[0] = KVR_OK or KVR_E_DOMAIN from a workspace status word.
 hipError_t launch_export_status(const int *status, int32_t *out, hipStream_t stream);
-hipError_t launch_upload(double *dst, const double *host_src, int64_t count, hipStream_t stream);
 // Clears the status word and zero[0..nzero), and stores three host tables.
 hipError_t launch_stage(int *status, double *const dst[3], const double *const src[3],
                         const int64_t cnt[3], unsigned *zero, int nzero, hipStream_t stream);
@@ -182,8 +181,8 @@ struct BinWs {
                                 // order, then inf
     int32_t *at;                // [K1 + P] thresholds strictly below each timer, then each deadline
     unsigned long long *bins;   // [M + 1][copies][4] sums over the waits of each bin
-    int64_t *cumN;              // [M + 1] prefix sums over the bins (grids of many policies)
-    double *cumS;
+    int64_t *cumN;              // [M + 1] prefix sums within each tile of bins, then the tiles'
+    double *cumS;               // totals (grids of many policies)
     int M;                      // thresholds
     int copies;                 // of each bin
     int bucket0;                // first bucket of the search table
