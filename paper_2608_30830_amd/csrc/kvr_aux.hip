@@ -274,13 +274,26 @@ hipError_t launch_xg(const SampleSrc &src, int64_t R, const Tables &tb, double *
 // ---------------------------------------------------- split reduce, finalize --
 // Partials are laid out [split][resample][tile][value][policy] with the LT
 // load accumulators as values (R3 comes from the deadline bins of
-// kvr_r3.hip, X and G from xg_kernel).  Stage 1: one thread per
-// element of split 0 sums it over the splits, in split order, in place.
-__global__ void __launch_bounds__(256) reduce_splits_kernel(int64_t nsplit, int64_t slice,
-                                                            double *__restrict__ partials)
+// kvr_r3.hip, X and G from xg_kernel).  One thread per element of split 0 sums
+// it over the splits, in split order, and turns the sum into a mean cost with the
+// expression of the fused grid kernel.  Memory-bound; with the sums written back
+// and finished by a second kernel 1,024 x 65,536 draws took 20 us more and 37 x
+// 5,003 a launch of 5 us.
+template <typename I>   // the narrowest index type that holds slice: its divisions count here
+__global__ void __launch_bounds__(256) reduce_splits_kernel(GridPlan plan, Tables tb, PriceDev pr,
+                                                            double md, int64_t slice,
+                                                            const double *__restrict__ X,
+                                                            const double *__restrict__ G, R3Ws r3s,
+                                                            const double *__restrict__ partials,
+                                                            double *__restrict__ cost_out)
 {
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (gid >= slice) return;
+    const I P = (I)tb.K1 * (I)tb.K2, row = (I)gid / P, f = (I)gid - row * P;
+    const I tile_row = row / (I)plan.LT, r = tile_row / (I)plan.ntiles;
+    const int lg = (int)(tile_row - r * (I)plan.ntiles) * plan.LT + (int)(row - tile_row * (I)plan.LT);
+    if (lg >= tb.L) return;   // the padding of the last tile
+    const int64_t nsplit = plan.nsplit;
     double s = partials[gid];
     int64_t q = 1;
     for (; q + 8 <= nsplit; q += 8) {   // eight loads in flight, added in split order
@@ -291,34 +304,12 @@ __global__ void __launch_bounds__(256) reduce_splits_kernel(int64_t nsplit, int6
         for (int u = 0; u < 8; ++u) s += v[u];
     }
     for (; q < nsplit; ++q) s += partials[q * slice + gid];
-    partials[gid] = s;
-}
-
-// Stage 2: one thread per (resample, tile, policy) turns the sums into mean
-// costs, with the same expression the fused grid kernel uses.
-template <int LT>
-__global__ void __launch_bounds__(256) finalize_kernel(GridPlan plan, Tables tb, PriceDev pr,
-                                                       double md, const double *__restrict__ X,
-                                                       const double *__restrict__ G, R3Ws r3s,
-                                                       const double *__restrict__ sums,
-                                                       double *__restrict__ cost_out)
-{
-    const int64_t P = (int64_t)tb.K1 * tb.K2;
-    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= plan.R * plan.ntiles * P) return;
-    const int64_t f = gid % P;
-    const int tile = (int)((gid / P) % plan.ntiles);
-    const int64_t r = gid / (P * plan.ntiles);
-    const int a = (int)(f / tb.K2);
-    const int64_t base_row = (r * plan.ntiles + tile) * LT;
+    const int a = (int)(f / (I)tb.K2);
     const int32_t xb = r3s.lb[f];
-    const double r3 = (xb < r3s.nbins) ? (double)r3s.S[r * r3s.nbins + xb] : 0.0;
-    const double base = pr.a1 * X[r * tb.K1 + a] + (pr.b2 * (G[r * tb.K1 + a] - r3) + pr.b3 * r3);
-#pragma unroll
-    for (int l = 0; l < LT; ++l) {
-        const int lg = tile * LT + l;
-        if (lg < tb.L) cost_out[(r * tb.L + lg) * P + f] = (base + sums[(base_row + l) * P + f]) / md;
-    }
+    const double r3 = (xb < r3s.nbins) ? (double)r3s.S[(int64_t)r * r3s.nbins + xb] : 0.0;
+    const double x = X[(int64_t)r * tb.K1 + a], g = G[(int64_t)r * tb.K1 + a];
+    const double base = pr.a1 * x + (pr.b2 * (g - r3) + pr.b3 * r3);
+    cost_out[((int64_t)r * tb.L + lg) * (int64_t)P + f] = (base + s) / md;
 }
 
 hipError_t launch_reduce_partials(const GridPlan &plan, const Tables &tb, const PriceDev &pr,
@@ -327,20 +318,14 @@ hipError_t launch_reduce_partials(const GridPlan &plan, const Tables &tb, const 
 {
     const int64_t P = (int64_t)tb.K1 * tb.K2;
     const int64_t slice = plan.R * plan.ntiles * (int64_t)plan.LT * P;
-    hipLaunchKernelGGL(reduce_splits_kernel, dim3((unsigned)((slice + 255) / 256)), dim3(256), 0,
-                       stream, (int64_t)plan.nsplit, slice, partials);
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
-    const int64_t threads = plan.R * plan.ntiles * P;
-    const unsigned blocks = (unsigned)((threads + 255) / 256);
+    const dim3 grid((unsigned)((slice + 255) / 256));
     const double md = (double)m;
-    switch (plan.LT) {
-    case 4: hipLaunchKernelGGL(finalize_kernel<4>, dim3(blocks), dim3(256), 0, stream, plan, tb, pr, md, X, G, r3, partials, cost_out); break;
-    case 8: hipLaunchKernelGGL(finalize_kernel<8>, dim3(blocks), dim3(256), 0, stream, plan, tb, pr, md, X, G, r3, partials, cost_out); break;
-    case 16: hipLaunchKernelGGL(finalize_kernel<16>, dim3(blocks), dim3(256), 0, stream, plan, tb, pr, md, X, G, r3, partials, cost_out); break;
-    case 32: hipLaunchKernelGGL(finalize_kernel<32>, dim3(blocks), dim3(256), 0, stream, plan, tb, pr, md, X, G, r3, partials, cost_out); break;
-    default: return hipErrorInvalidValue;
-    }
+    if (slice < ((int64_t)1 << 31))
+        hipLaunchKernelGGL(reduce_splits_kernel<uint32_t>, grid, dim3(256), 0, stream, plan, tb, pr, md,
+                           slice, X, G, r3, partials, cost_out);
+    else
+        hipLaunchKernelGGL(reduce_splits_kernel<uint64_t>, grid, dim3(256), 0, stream, plan, tb, pr, md,
+                           slice, X, G, r3, partials, cost_out);
     return hipGetLastError();
 }
 

@@ -31,35 +31,19 @@ constexpr int kR3BinsPerPass = 16384;  // 128 KiB of LDS counters per pass
 constexpr int kR3BinsSmall = 2048;     // 16 KiB: grids with few deadlines
 constexpr int kR3Unroll = 4;           // draws per thread and step, fetched together
 constexpr int kR3LdsTable = 4096;      // timer-table entries staged in LDS (32 KiB)
+constexpr int64_t kR3ManyItems = 1 << 18;   // items whose own number fills the chip
 
 // Number of grid deadlines fl(t1[a] + t2[k]) strictly below x, from timer
-// tables t1[K1] and t2[K2] (in LDS when they fit there).
-__device__ int32_t deadlines_below(const double *t1v, int K1, const double *t2v, int K2, double x)
+// tables t1[K1] and t2[K2] (in LDS when they fit there), along the rows (or
+// columns, whichever are fewer) first, first + step, ...
+__device__ int32_t deadlines_below(const double *t1v, int K1, const double *t2v, int K2, double x,
+                                   int first, int step)
 {
     int32_t c = 0;
-    if (K1 <= K2) {
-        for (int a = 0; a < K1; ++a) {
-            const double t1 = t1v[a];
-            int lo = 0, hi = K2;   // first k with t1 + t2[k] >= x
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (t1 + t2v[mid] < x) lo = mid + 1;
-                else hi = mid;
-            }
-            c += lo;
-        }
-    } else {
-        for (int k = 0; k < K2; ++k) {
-            const double t2 = t2v[k];
-            int lo = 0, hi = K1;   // first a with t1[a] + t2 >= x
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (t1v[mid] + t2 < x) lo = mid + 1;
-                else hi = mid;
-            }
-            c += lo;
-        }
-    }
+    if (K1 <= K2)
+        for (int a = first; a < K1; a += step) c += rank_below(t2v, K2, t1v[a], x);
+    else
+        for (int k = first; k < K2; k += step) c += rank_below(t1v, K1, t2v[k], x);
     return c;
 }
 
@@ -69,11 +53,19 @@ __device__ int32_t deadlines_below(const double *t1v, int K1, const double *t2v,
 // that the passes over the draws gather one record per draw.  Items
 // n..n+P-1: per policy f = a*K2 + k, the number of grid deadlines strictly
 // below its own.
+// NL lanes share an item's searches: one binary search after another along each
+// of min(K1, K2) rows is a chain of dependent reads (5,003 samples with nine rows:
+// 10.6 us by one lane, 5.0 by eight).  Also clears zero[0..nzero).
+template <int NL>
 __global__ void __launch_bounds__(256) r3_bins_kernel(const double *__restrict__ w,
                                                       const int32_t *__restrict__ T, int64_t n,
                                                       Tables tb, SampleRec *__restrict__ rec,
-                                                      int32_t *__restrict__ lb)
+                                                      int32_t *__restrict__ lb,
+                                                      unsigned long long *__restrict__ zero,
+                                                      int64_t nzero)
 {
+    const int64_t me = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t z = me; z < nzero; z += (int64_t)gridDim.x * blockDim.x) zero[z] = 0ull;
     // the timer tables in LDS when both fit (every item searches them)
     __shared__ double lt[kR3LdsTable];
     const bool in_lds = tb.K1 + tb.K2 <= kR3LdsTable;   // uniform
@@ -85,7 +77,13 @@ __global__ void __launch_bounds__(256) r3_bins_kernel(const double *__restrict__
         t1v = lt;
         t2v = lt + tb.K1;
     }
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = me / NL;
+    const int lane = (int)(threadIdx.x % NL);
+    auto below = [&](double x) {   // every lane of the item takes part
+        int32_t c = deadlines_below(t1v, tb.K1, t2v, tb.K2, x, lane, NL);
+        for (int off = NL / 2; off > 0; off >>= 1) c += __shfl_xor(c, off, NL);
+        return c;
+    };
     const int64_t P = (int64_t)tb.K1 * tb.K2;
     if (i < n) {
         double x = w[i];
@@ -94,22 +92,16 @@ __global__ void __launch_bounds__(256) r3_bins_kernel(const double *__restrict__
         int32_t t = T[i];
         if (t < 1) t = 1;
         SampleRec v;
-        v.bin = deadlines_below(t1v, tb.K1, t2v, tb.K2, x + 0.0);
+        v.bin = below(x + 0.0);
         v.T = t;
         v.w = x + 0.0;
-        rec[i] = v;
+        if (lane == 0) rec[i] = v;
     } else if (i - n < P) {
         const int64_t f = i - n;
         const int a = (int)(f / tb.K2), k = (int)(f % tb.K2);
-        lb[f] = deadlines_below(t1v, tb.K1, t2v, tb.K2, t1v[a] + t2v[k]);
+        const int32_t c = below(t1v[a] + t2v[k]);
+        if (lane == 0) lb[f] = c;
     }
-}
-
-__global__ void __launch_bounds__(256) r3_zero_kernel(unsigned long long *__restrict__ p,
-                                                      int64_t count)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) p[i] = 0ull;
 }
 
 // One block per (resample, split of its draws): histogram of T over the
@@ -274,17 +266,18 @@ hipError_t launch_r3(const SampleSrc &src, int64_t R, const Tables &tb, const R3
                      double *X, double *G, int *status, hipStream_t stream)
 {
     const int64_t P = (int64_t)tb.K1 * tb.K2;
-    hipLaunchKernelGGL(r3_bins_kernel, dim3((unsigned)((src.n + P + 255) / 256)), dim3(256), 0,
-                       stream, src.w, src.T, src.n, tb, ws.rec, ws.lb);
+    // several histogram blocks per resample add into cleared rows
+    const int64_t nzero = ws.nsplit > 1 ? R * ws.nbins : 0;
+    const int64_t items = src.n + P;
+    if ((tb.K1 < tb.K2 ? tb.K1 : tb.K2) < 4 || items > kR3ManyItems)
+        hipLaunchKernelGGL(r3_bins_kernel<1>, dim3((unsigned)((items + 255) / 256)), dim3(256), 0,
+                           stream, src.w, src.T, src.n, tb, ws.rec, ws.lb, ws.S, nzero);
+    else
+        hipLaunchKernelGGL(r3_bins_kernel<8>, dim3((unsigned)((items + 31) / 32)), dim3(256), 0,
+                           stream, src.w, src.T, src.n, tb, ws.rec, ws.lb, ws.S, nzero);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
     if (ws.nbins == 0) return hipSuccess;   // every deadline infinite: R3 = 0
-    if (ws.nsplit > 1) {
-        const int64_t cnt = R * ws.nbins;
-        hipLaunchKernelGGL(r3_zero_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0,
-                           stream, ws.S, cnt);
-        if ((err = hipGetLastError()) != hipSuccess) return err;
-    }
     const bool xg = X != nullptr;   // r3_fuses_xg held on the host
     const double *t1 = tb.t1;
     const dim3 grid((unsigned)(R * ws.nsplit)), block(kR3Threads);
