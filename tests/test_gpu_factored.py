@@ -256,3 +256,35 @@ def test_factored_exact_tie_rule(kvr, oracle_mod, name, k1):
         assert_costs(cost[r], ref)
         rb, _, _ = oracle_mod.select(ref, wl.t2)
         assert np.array_equal(best[r], rb), (r, best[r], rb)
+
+
+# (n, k1, k2, L, R, m): base samples around a tile of 2,048 positions, around a
+# wave's 512 and up to the 65,536 of the packed counters and one more (the general
+# kernel); rows of m draws that start at every 4-byte phase and rows shorter than
+# one aligned read; query positions denser than the 108 records a wave stages;
+# policies one by one and in groups of four (1,024 policies and rows of 8 on), with
+# rows that leave a remainder; load tiles of 16 and of 32, full and with a remainder.
+EDGES = [(2047, 5, 205, 17, 5, 1003), (2048, 64, 16, 16, 4, 2), (2049, 3, 683, 32, 4, 2049),
+         (513, 2, 511, 1, 5, 1), (4096, 1, 1025, 33, 3, 4097), (1, 70, 16, 3, 4, 3),
+         (600, 120, 9, 5, 3, 31), (600, 150, 7, 5, 3, 31),
+         (65535, 37, 29, 16, 3, 5001), (65536, 7, 147, 31, 3, 5002), (65537, 7, 147, 31, 3, 5002)]
+
+
+@pytest.mark.parametrize("case", EDGES)
+def test_factored_small_edges(kvr, oracle_mod, case):
+    """Every cost and selection against the oracle's closed form of the row, within
+    the tolerances the other factored tests use: both round a sum of at most m
+    products, far inside 1e-9 relative at these m."""
+    n, k1, k2, L, R, m = case
+    wl = workloads.random_case(220 + n % 7, n, k1, k2, L, resamples=R, m=m, ties=True)
+    best, bc, cost = (_np(x) for x in _factored(kvr, wl, want_cost=True))
+    pr = oracle_mod.workload_prices(wl)
+    for r in range(R):
+        ref = oracle_mod.closed_form_grid(wl.wait_s, wl.ctx_tokens, pr, wl.t1, wl.t2, wl.lam,
+                                          idx_row=wl.idx[r])
+        assert_costs(cost[r], ref)
+        rb, rbc, _ = oracle_mod.select(ref, wl.t2)
+        assert_selection(ref, best[r], rb)
+        assert_costs(bc[r], rbc)
+    best2, bc2 = (_np(x) for x in _factored(kvr, wl))
+    assert np.array_equal(best2, best) and np.array_equal(bc2, bc)
