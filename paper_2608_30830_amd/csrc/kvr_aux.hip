@@ -279,7 +279,6 @@ hipError_t launch_xg(const SampleSrc &src, int64_t R, const Tables &tb, double *
 // expression of the fused grid kernel.  Memory-bound; with the sums written back
 // and finished by a second kernel 1,024 x 65,536 draws took 20 us more and 37 x
 // 5,003 a launch of 5 us.
-template <typename I>   // the narrowest index type that holds slice: its divisions count here
 __global__ void __launch_bounds__(256) reduce_splits_kernel(GridPlan plan, Tables tb, PriceDev pr,
                                                             double md, int64_t slice,
                                                             const double *__restrict__ X,
@@ -289,9 +288,9 @@ __global__ void __launch_bounds__(256) reduce_splits_kernel(GridPlan plan, Table
 {
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (gid >= slice) return;
-    const I P = (I)tb.K1 * (I)tb.K2, row = (I)gid / P, f = (I)gid - row * P;
-    const I tile_row = row / (I)plan.LT, r = tile_row / (I)plan.ntiles;
-    const int lg = (int)(tile_row - r * (I)plan.ntiles) * plan.LT + (int)(row - tile_row * (I)plan.LT);
+    const uint32_t P = (uint32_t)tb.K1 * (uint32_t)tb.K2, row = (uint32_t)gid / P, f = (uint32_t)gid - row * P;
+    const uint32_t tile_row = row / (uint32_t)plan.LT, r = tile_row / (uint32_t)plan.ntiles;
+    const int lg = (int)(tile_row - r * (uint32_t)plan.ntiles) * plan.LT + (int)(row - tile_row * (uint32_t)plan.LT);
     if (lg >= tb.L) return;   // the padding of the last tile
     const int64_t nsplit = plan.nsplit;
     double s = partials[gid];
@@ -304,7 +303,7 @@ __global__ void __launch_bounds__(256) reduce_splits_kernel(GridPlan plan, Table
         for (int u = 0; u < 8; ++u) s += v[u];
     }
     for (; q < nsplit; ++q) s += partials[q * slice + gid];
-    const int a = (int)(f / (I)tb.K2);
+    const int a = (int)(f / (uint32_t)tb.K2);
     const int32_t xb = r3s.lb[f];
     const double r3 = (xb < r3s.nbins) ? (double)r3s.S[(int64_t)r * r3s.nbins + xb] : 0.0;
     const double x = X[(int64_t)r * tb.K1 + a], g = G[(int64_t)r * tb.K1 + a];
@@ -320,12 +319,10 @@ hipError_t launch_reduce_partials(const GridPlan &plan, const Tables &tb, const 
     const int64_t slice = plan.R * plan.ntiles * (int64_t)plan.LT * P;
     const dim3 grid((unsigned)((slice + 255) / 256));
     const double md = (double)m;
-    if (slice < ((int64_t)1 << 31))
-        hipLaunchKernelGGL(reduce_splits_kernel<uint32_t>, grid, dim3(256), 0, stream, plan, tb, pr, md,
-                           slice, X, G, r3, partials, cost_out);
-    else
-        hipLaunchKernelGGL(reduce_splits_kernel<uint64_t>, grid, dim3(256), 0, stream, plan, tb, pr, md,
-                           slice, X, G, r3, partials, cost_out);
+    // Two splits or more stay under the partial sums' 1 GiB: slice <= 2^26.
+    if (slice >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(reduce_splits_kernel, grid, dim3(256), 0, stream, plan, tb, pr, md, slice, X,
+                       G, r3, partials, cost_out);
     return hipGetLastError();
 }
 

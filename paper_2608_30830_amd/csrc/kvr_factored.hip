@@ -25,9 +25,10 @@
 // resamples: factored_prefix_kernel (one block per resample, four per CU: the
 // draws' multiplicities per base sample in LDS, then, from LDS, a fixed-order
 // scan of the weights c_k T_k (exact) and c_k T_k w_k over the positions that
-// records N and S only at the query positions), factored_policy_kernel (one
-// block per (resample, tile of 32 or 16 loads): every policy from its two slots,
-// fused arg-min on the numerators m*C).
+// records N and S only at the query positions; up to 65,536 base samples
+// factored_prefix_small_kernel, the same sums in the same order in fewer
+// instructions), factored_policy_kernel (one block per (resample, tile of 32 or
+// 16 loads): every policy from its two slots, fused arg-min on the numerators m*C).
 #include "kvr_device.h"
 #include "kvr_dpp.h"
 #include "kvr_factored.h"
@@ -934,9 +935,11 @@ hipError_t launch_factored(const SampleSrc &src, int64_t R, const Tables &tb, co
     if ((err = hipGetLastError()) != hipSuccess) return err;
     const int FL = tb.L <= 16 ? 16 : kFLoads;                 // loads per policy block
     const int ntl = (tb.L + FL - 1) / FL;
-    // groups of four host timers where rows hold a few and one chunk of them is
-    // full; fewer policies keep a thread each
-    const int U = tb.K2 >= 16 && P >= 4 * kFPolThreads ? 4 : 1;
+    // Groups of four host timers from where they fill a chunk on; fewer policies
+    // keep a thread each (calls of 1,024 rows x 9,000 draws by U = 1 and 4: 1 x 257
+    // policies 122.6 and 125.5 us, 4 x 257 127.1 and 131.1, 128 x 8 133.6 and 133.0,
+    // 64 x 16 equal, 256 x 16 160.9 and 152.2, 512 x 8 166.1 and 157.4).
+    const int U = tb.K2 >= 8 && P >= 4 * kFPolThreads ? 4 : 1;
     const int lcp = policy_columns(tb.K1, (tb.K2 + U - 1) / U);
     for (int64_t r0 = 0; r0 < R; r0 += ws.Rb) {
         const int64_t rb = (R - r0 < ws.Rb) ? R - r0 : ws.Rb;

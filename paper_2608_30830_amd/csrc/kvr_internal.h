@@ -202,14 +202,14 @@ hipError_t launch_binned(const double *w, const int32_t *T, int64_t n, const Tab
 struct SortWs {
     uint64_t *keys[2];
     int32_t *vals[2];
-    uint32_t *hist;       // [256][nblocks]
+    uint32_t *hist;       // [256][nblocks], or 16-bit [nblocks][256]
     uint32_t *counts;     // [256] digit totals of the current pass
     int64_t *Nsum;        // [n] inclusive prefix of T (sorted order)
     double *Ssum;         // [n] the same for T*w
     int64_t *blkN;        // [nblocks_scan]
     double *blkS;         // [nblocks_scan]
     int nblocks;          // sort tiles
-    int kpt;              // keys per thread of a sort tile (tile = 256 * kpt keys)
+    int threads, kpt;     // a sort tile holds threads * kpt keys
     int nblocks_scan;     // scan tiles
 };
 

@@ -12,8 +12,9 @@
 //
 // Sort: keys are the bits of w + 0.0 (waits are >= 0, so unsigned order of
 // the bits is numeric order and -0.0 sorts as +0.0).  Eight 8-bit digit
-// passes, each reduce-then-scan (tile histograms, one exclusive scan, a
-// ranking scatter); no inter-workgroup waiting, so no forward-progress
+// passes, each reduce-then-scan (tile histograms, one exclusive scan, which up
+// to 2^20 keys every block of the scatter does for itself, a ranking scatter);
+// no inter-workgroup waiting, so no forward-progress
 // assumption.  Ranking inside a tile is stable: a wave ranks its keys with a
 // ballot match on the digit, in input order.  The first pass reads the waits
 // themselves (its histograms come straight from them, so no key array is
@@ -42,23 +43,35 @@ constexpr int kScanTile = kScanThreads * kScanIPT;
 static inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Keys per thread of the multi-block sort: the largest tile (256 * kpt keys,
-// kpt = 2, 4, 8 or 16) that still gives about one block per CU, since below
-// that each pass is bound by the length of a block's chain (measured on
-// MI355X: 65,536 keys 0.150 ms with kpt = 2 against 0.203 ms with 8; 2^20
-// keys 0.31 ms with 8 against 0.41 ms with 2).  Longer tiles also give each
-// digit longer runs of consecutive destinations: at 2^24 keys a scatter pass
-// writes exactly its 24 algorithmic bytes per key with 4,096-key tiles (103 us)
-// and 12-37 % more with 2,048-key tiles (129-134 us); at 2^22 keys the shorter
-// tiles still win (23.4 against 29.4 us), having twice the blocks.
+// Tile of the multi-block sort, threads * kpt keys.  Up to 2^20 keys a pass is
+// bound by its launches and by the length of a block's chain, so the tiles are the
+// shortest that leave at most 256 of them, whose counts every scatter block then
+// sums itself (FOLD), with few keys per thread: calls with an order requested,
+// with 256-thread tiles and a scan launch before and now, in us: 2,049 waits 93 and
+// 73, 65,536 98 and 82, 131,072 104 and 88, 2^18 119 and 102, 2^19 150 and 126, 2^20
+// 188 and 177 (eight keys for each of 512 threads 185; beyond, 256 tiles would not
+// fit LDS).  At 2^17 512 threads measured 88 against 96 for 256, at 200,000 95 against
+// 97 for 1,024.  Counting the next digit in the scatter (an atomic per key into its
+// destination's tile) in place of the histogram launches: 66 us at 5,003 waits but
+// 92 at 65,536 and 168 at 2^18.  Longer tiles give each
+constexpr int64_t kFoldTo = int64_t(1) << 20;
+constexpr int kFoldTiles = 256;
+
+static int sort_threads(int64_t n)
+{
+    if (n > kFoldTo) return kSortThreads;
+    return n <= (int64_t(1) << 16) ? 256 : n <= (int64_t(1) << 18) ? 512 : 1024;
+}
+
 static int sort_kpt(int64_t n)
 {
-    return n >= (int64_t(1) << 23) ? 16 : n >= (int64_t(1) << 19) ? 8 : n >= (int64_t(1) << 18) ? 4 : 2;
+    if (n > kFoldTo) return n >= (int64_t(1) << 23) ? 16 : 8;
+    return n > (int64_t(1) << 19) ? 4 : 2;
 }
 
 size_t sort_ws_bytes(int64_t n)
 {
-    const int64_t nb = cdiv(n, kSortThreads * sort_kpt(n)), ns = cdiv(n, kScanTile);
+    const int64_t nb = cdiv(n, sort_threads(n) * sort_kpt(n)), ns = cdiv(n, kScanTile);
     size_t b = 0;
     b += 2 * align256(sizeof(uint64_t) * n);
     b += 2 * align256(sizeof(int32_t) * n);
@@ -75,7 +88,8 @@ void sort_ws_carve(void *base, int64_t n, SortWs &ws)
 {
     char *p = static_cast<char *>(base);
     ws.kpt = sort_kpt(n);
-    ws.nblocks = (int)cdiv(n, kSortThreads * ws.kpt);
+    ws.threads = sort_threads(n);
+    ws.nblocks = (int)cdiv(n, ws.threads * ws.kpt);
     ws.nblocks_scan = (int)cdiv(n, kScanTile);
     auto take = [&](size_t bytes) {
         char *q = p;
@@ -116,33 +130,43 @@ __device__ __forceinline__ uint64_t wait_key(double x, bool &bad)
     return b;
 }
 
+// A tile's digit counts: digit-major 32-bit words for digit_scan_kernel, or
+// (FOLD) tile-major 16-bit words, which every scatter block sums itself.
+template <bool FOLD>
+__device__ __forceinline__ void store_tile_counts(const uint32_t *h, void *hist, int tile, int nblocks)
+{
+    if (threadIdx.x >= 256) return;
+    const uint32_t c = h[threadIdx.x];
+    if (FOLD) static_cast<uint16_t *>(hist)[(int64_t)tile * 256 + threadIdx.x] = (uint16_t)c;
+    else static_cast<uint32_t *>(hist)[(int64_t)threadIdx.x * nblocks + tile] = c;
+}
+
 // Tile histograms of the first digit straight from the waits (domain-checked
 // on the bits), so that the first scatter can read the waits and context
 // sizes itself and no key array is written before it.  Tiles are those of the
-// digit passes (256 * KPT keys); digit-major histogram hist[d * nblocks + tile].
-template <int KPT>
-__global__ void __launch_bounds__(kSortThreads) sort_first_hist_kernel(
-    const double *__restrict__ w, int64_t n, uint32_t *__restrict__ hist, int nblocks,
-    int *status)
+// digit passes (THREADS * KPT keys).
+template <int THREADS, int KPT, bool FOLD>
+__global__ void __launch_bounds__(THREADS) sort_first_hist_kernel(
+    const double *__restrict__ w, int64_t n, void *__restrict__ hist, int nblocks, int *status)
 {
     __shared__ uint32_t h[256];
-    h[threadIdx.x] = 0;
+    if (threadIdx.x < 256) h[threadIdx.x] = 0;
     __syncthreads();
     const int tile = sort_tile(nblocks);
-    const int64_t base = (int64_t)tile * (kSortThreads * KPT);
+    const int64_t base = (int64_t)tile * (THREADS * KPT);
     double x[KPT];
 #pragma unroll
     for (int q = 0; q < KPT; ++q) {   // every load in flight before counting
-        const int64_t i = base + q * kSortThreads + threadIdx.x;
+        const int64_t i = base + q * THREADS + threadIdx.x;
         x[q] = i < n ? w[i] : 0.0;
     }
     bool bad = false;
 #pragma unroll
     for (int q = 0; q < KPT; ++q)
-        if (base + q * kSortThreads + threadIdx.x < n) atomicAdd(&h[wait_key(x[q], bad) & 255u], 1u);
+        if (base + q * THREADS + threadIdx.x < n) atomicAdd(&h[wait_key(x[q], bad) & 255u], 1u);
     if (bad) flag_domain(status);
     __syncthreads();
-    hist[(int64_t)threadIdx.x * nblocks + tile] = h[threadIdx.x];
+    store_tile_counts<FOLD>(h, hist, tile, nblocks);
 }
 
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask)
@@ -164,32 +188,30 @@ __device__ __forceinline__ uint64_t digit_peers(uint32_t d, bool valid)
     return peers;
 }
 
-// Per-tile digit histogram (tiles of 256 * KPT keys), digit-major:
-// hist[d * nblocks + tile].  The keys of a wave that share the first lane's
-// digit add their count through that lane, the others one by one: when most
+// Per-tile digit histogram (tiles of THREADS * KPT keys).  The keys of a wave
+// that share the first lane's digit add their count through that lane, the others one by one: when most
 // keys hold one digit (the high bytes of waits spread over a few binades)
 // this replaces up to 64 atomics on one LDS word by one.
-template <int KPT>
-__global__ void __launch_bounds__(kSortThreads) sort_hist_kernel(const uint64_t *__restrict__ keys,
-                                                                 int64_t n, int shift,
-                                                                 uint32_t *__restrict__ hist,
-                                                                 int nblocks)
+template <int THREADS, int KPT, bool FOLD>
+__global__ void __launch_bounds__(THREADS) sort_hist_kernel(const uint64_t *__restrict__ keys,
+                                                            int64_t n, int shift,
+                                                            void *__restrict__ hist, int nblocks)
 {
     __shared__ uint32_t h[256];
-    h[threadIdx.x] = 0;
+    if (threadIdx.x < 256) h[threadIdx.x] = 0;
     __syncthreads();
     const int tile = sort_tile(nblocks);
-    const int64_t base = (int64_t)tile * (kSortThreads * KPT);
+    const int64_t base = (int64_t)tile * (THREADS * KPT);
     uint64_t key[KPT];
 #pragma unroll
     for (int q = 0; q < KPT; ++q) {
-        const int64_t i = base + q * kSortThreads + threadIdx.x;
+        const int64_t i = base + q * THREADS + threadIdx.x;
         key[q] = i < n ? keys[i] : 0;
     }
     const int lane = threadIdx.x % kWave;
 #pragma unroll
     for (int q = 0; q < KPT; ++q) {
-        const bool valid = base + q * kSortThreads + threadIdx.x < n;
+        const bool valid = base + q * THREADS + threadIdx.x < n;
         const uint32_t d = (uint32_t)(key[q] >> shift) & 255u;
         const uint32_t d0 = __builtin_amdgcn_readfirstlane(d);
         const uint64_t same = __ballot(valid && d == d0);
@@ -197,7 +219,7 @@ __global__ void __launch_bounds__(kSortThreads) sort_hist_kernel(const uint64_t 
         else if (valid && d != d0) atomicAdd(&h[d], 1u);
     }
     __syncthreads();
-    hist[(int64_t)threadIdx.x * nblocks + tile] = h[threadIdx.x];
+    store_tile_counts<FOLD>(h, hist, tile, nblocks);
 }
 
 // The same histogram from the digit bytes that the previous pass's scatter
@@ -237,20 +259,43 @@ __global__ void __launch_bounds__(kSortThreads) sort_hist_bytes_kernel(
     hist[(int64_t)threadIdx.x * nblocks + tile] = h[threadIdx.x];
 }
 
-// Exclusive scan, within one block of 256 threads, of one value per thread;
-// returns the prefix and writes the block total to *total (all threads).
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *total)
+// Exclusive scan over the first 256 threads of a block (the digits) of one
+// value per thread; the prefix of the other threads means nothing.
+__device__ __forceinline__ uint32_t digit_exclusive_scan(uint32_t v)
 {
     __shared__ uint32_t wsum[4];
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     const uint32_t x = wave_incl_scan(v);
-    if (lane == kWave - 1) wsum[wave] = x;
+    if (lane == kWave - 1 && wave < 4) wsum[wave] = x;
     __syncthreads();
     uint32_t before = 0;
-    for (int q = 0; q < wave; ++q) before += wsum[q];
-    *total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    for (int q = 0; q < 4; ++q) before += q < wave ? wsum[q] : 0u;
     __syncthreads();
     return before + x - v;
+}
+
+// Sums over tiles [t0, t1) of the digit counts at hist[tile][8 * column ..],
+// the tiles taken in turn by the block's 32-thread groups.  Eight rows are in
+// flight and added as 16-bit words: 8 * 4,096 counts fit.
+typedef uint16_t Counts8 __attribute__((ext_vector_type(8)));
+
+template <int GROUPS>
+__device__ __forceinline__ void add_tile_counts(const Counts8 *__restrict__ hist, int t0, int t1,
+                                                uint32_t (&sum)[8])
+{
+    const int group = threadIdx.x / 32, col = threadIdx.x % 32;
+    for (int t = t0 + group; t < t1; t += 8 * GROUPS) {
+        Counts8 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int tu = t + u * GROUPS;
+            v[u] = tu < t1 ? hist[(int64_t)tu * 32 + col] : (Counts8)0;
+        }
+#pragma unroll
+        for (int u = 1; u < 8; ++u) v[0] += v[u];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) sum[c] += v[0][c];
+    }
 }
 
 // Exclusive scan over the 1,024 threads of a block of one value per thread
@@ -326,11 +371,15 @@ __global__ void __launch_bounds__(1024) digit_scan_kernel(uint32_t *__restrict__
 // digit_scan_kernel) + (keys with its digit earlier in this tile).  The tile
 // is first reordered by digit in LDS, then written out in that order, so
 // consecutive threads store consecutive addresses within each digit's run.
-template <int KPT, bool FIRST>
-__global__ void __launch_bounds__(kSortThreads) sort_scatter_kernel(
+// FOLD: the block sums the counts of all tiles and of the earlier ones from the
+// tile-major histogram (at most 256 tiles, 512 B each, its reads under way with the
+// keys') instead of reading them from digit_scan_kernel: a scan
+// launch costs 4.5 us a pass, the sums about 2.
+template <int THREADS, int KPT, bool FIRST, bool FOLD>
+__global__ void __launch_bounds__(THREADS) sort_scatter_kernel(
     const uint64_t *__restrict__ keys_in, const int32_t *__restrict__ vals_in,
     const double *__restrict__ w, const int32_t *__restrict__ T, int payload_T, int64_t n,
-    int shift, const uint32_t *__restrict__ offs, const uint32_t *__restrict__ totals, int nblocks,
+    int shift, const void *__restrict__ offs, const uint32_t *__restrict__ totals, int nblocks,
     uint64_t *__restrict__ keys_out, int32_t *__restrict__ vals_out, uint8_t *__restrict__ dig_out,
     int *status)
 {
@@ -340,25 +389,22 @@ __global__ void __launch_bounds__(kSortThreads) sort_scatter_kernel(
     // most 64 * KPT keys, a tile at most 4,096, and a destination fits 32 bits
     // (n < 2^31).  wcnt holds the waves' digit counts, then, in place, each
     // wave's first tile position within its digit (wofs)
-    __shared__ uint16_t wcnt[4][256];
+    static_assert(THREADS * KPT <= 4096, "add_tile_counts adds eight tiles in 16 bits");
+    constexpr int kWaves = THREADS / kWave;
+    __shared__ alignas(16) uint16_t wcnt[kWaves][256];
     auto &wofs = wcnt;
     __shared__ int32_t gbase[256];                   // destination of digit d's first tile key
-    constexpr int kTile = kSortThreads * KPT, kWaveK = kWave * KPT;
+    constexpr int kTile = THREADS * KPT, kWaveK = kWave * KPT;
     __shared__ uint64_t lkey[kTile];
     __shared__ int32_t lval[kTile];
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     const int tile = sort_tile(nblocks);
     // this tile's offset within digit threadIdx.x, loaded early (its latency
     // overlaps the ranking below)
-    const uint32_t my_off = offs[(int64_t)threadIdx.x * nblocks + tile];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) wcnt[q][threadIdx.x] = 0;
-    uint32_t dbase;
-    {
-        uint32_t all;
-        dbase = block_exclusive_scan(totals[threadIdx.x], &all);
-    }
-    __syncthreads();
+    uint32_t my_off = 0;
+    if (!FOLD)
+        my_off = static_cast<const uint32_t *>(offs)[(int64_t)threadIdx.x * nblocks + tile];
+    for (int q = threadIdx.x; q < kWaves * 128; q += THREADS) reinterpret_cast<uint32_t *>(wcnt)[q] = 0;
 
     const int64_t base = (int64_t)tile * kTile + (int64_t)wave * kWaveK;
     uint64_t key[KPT];
@@ -392,6 +438,33 @@ __global__ void __launch_bounds__(kSortThreads) sort_scatter_kernel(
             val[j] = i < n ? vals_in[i] : 0;
         }
     }
+    uint32_t dbase;   // keys with a digit below threadIdx.x
+    if (FOLD) {
+        __shared__ uint32_t part[2][kWaves][256];
+        const Counts8 *h = static_cast<const Counts8 *>(offs);
+        uint32_t before[8] = {}, after[8] = {};
+        add_tile_counts<THREADS / 32>(h, 0, tile, before);
+        add_tile_counts<THREADS / 32>(h, tile, nblocks, after);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {   // a wave holds two groups
+            before[c] += __shfl_xor(before[c], 32, kWave);
+            after[c] += __shfl_xor(after[c], 32, kWave);
+            part[lane / 32][wave][(lane % 32) * 8 + c] = lane < 32 ? before[c] : after[c];
+        }
+        __syncthreads();
+        uint32_t total = 0;
+        if (threadIdx.x < 256) {
+#pragma unroll
+            for (int q = 0; q < kWaves; ++q) {
+                my_off += part[0][q][threadIdx.x];
+                total += part[1][q][threadIdx.x];
+            }
+            total += my_off;
+        }
+        dbase = digit_exclusive_scan(total);
+    } else {
+        dbase = digit_exclusive_scan(totals[threadIdx.x]);   // its barriers also cover wcnt
+    }
 #pragma unroll
     for (int j = 0; j < KPT; ++j) {
         const bool valid = base + j * kWave + lane < n;
@@ -407,22 +480,25 @@ __global__ void __launch_bounds__(kSortThreads) sort_scatter_kernel(
     __syncthreads();
     {
         const int d = threadIdx.x;
-        uint32_t cnt[4], run = 0;
+        uint32_t cnt[kWaves], run = 0;
+        if (d < 256) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            cnt[q] = wcnt[q][d];
-            run += cnt[q];
+            for (int q = 0; q < kWaves; ++q) {
+                cnt[q] = wcnt[q][d];
+                run += cnt[q];
+            }
         }
-        uint32_t all;
-        const uint32_t tstart = block_exclusive_scan(run, &all);   // run = this tile's count of digit d
+        const uint32_t tstart = digit_exclusive_scan(run);   // run = this tile's count of digit d
         // wofs holds tile positions: digit d's run starts at tstart
-        uint32_t at = tstart;
+        if (d < 256) {
+            uint32_t at = tstart;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            wofs[q][d] = (uint16_t)at;
-            at += cnt[q];
+            for (int q = 0; q < kWaves; ++q) {
+                wofs[q][d] = (uint16_t)at;
+                at += cnt[q];
+            }
+            gbase[d] = (int32_t)((int64_t)dbase + my_off - tstart);
         }
-        gbase[d] = (int32_t)((int64_t)dbase + my_off - tstart);
     }
     __syncthreads();
     // tile positions are dense: the valid keys of the tile fill [0, nvalid)
@@ -444,14 +520,15 @@ __global__ void __launch_bounds__(kSortThreads) sort_scatter_kernel(
     const int nvalid = left < kTile ? (int)left : kTile;
 #pragma unroll
     for (int q = 0; q < KPT; ++q) {
-        const int pos = q * kSortThreads + (int)threadIdx.x;
+        const int pos = q * THREADS + (int)threadIdx.x;
         if (pos < nvalid) {
             const uint64_t k = lkey[pos];
             const int64_t dest = (int64_t)gbase[(k >> shift) & 255u] + pos;
             if (dest >= 0 && dest < n) {  // always true when the histograms agree
                 keys_out[dest] = k;
                 vals_out[dest] = lval[pos];
-                if (dig_out != nullptr) dig_out[dest] = (uint8_t)(k >> (shift + 8));   // uniform
+                if (!FOLD && dig_out != nullptr)   // uniform
+                    dig_out[dest] = (uint8_t)(k >> (shift + 8));
             }
         }
     }
@@ -933,7 +1010,7 @@ static size_t scatter_lds_pad(int kpt, int64_t n)
     return (kpt == 16 && n >= (int64_t(1) << 24)) ? 4096 : 0;
 }
 
-template <int KPT>
+template <int THREADS, int KPT, bool FOLD>
 static hipError_t launch_digit_passes(const double *w, const int32_t *T, int64_t n, SortWs &ws,
                                       int payload_T, int *status, hipStream_t stream)
 {
@@ -944,8 +1021,10 @@ static hipError_t launch_digit_passes(const double *w, const int32_t *T, int64_t
     // scatter 99.3 -> 107.7 us, the call 1.227 -> 1.160 ms; at 2^20 the
     // scatter's extra stores cost more than the histogram saves (12.8 -> 15.3
     // against 4.9 -> 4.2 us).
-    uint8_t *const dig = n >= kDigitBytesFrom ? reinterpret_cast<uint8_t *>(ws.Nsum) : nullptr;
-    if ((int64_t)ws.nblocks * kSortThreads * KPT > 8 * n) return hipErrorInvalidValue;
+    uint8_t *const dig = !FOLD && n >= kDigitBytesFrom ? reinterpret_cast<uint8_t *>(ws.Nsum) : nullptr;
+    const int64_t slots = (int64_t)ws.nblocks * THREADS * KPT;
+    if (slots < n || slots > 8 * n || (FOLD && ws.nblocks > kFoldTiles))
+        return hipErrorInvalidValue;
     const size_t pad = scatter_lds_pad(KPT, n);
     hipError_t err = hipSuccess;
     // pass p reads buffer (p & 1) and writes the other; the first reads the
@@ -953,25 +1032,28 @@ static hipError_t launch_digit_passes(const double *w, const int32_t *T, int64_t
     for (int pass = 0; pass < 8 && err == hipSuccess; ++pass) {
         const int shift = 8 * pass, in = pass & 1, out = in ^ 1;
         if (pass == 0)
-            hipLaunchKernelGGL(sort_first_hist_kernel<KPT>, dim3(ws.nblocks), dim3(kSortThreads),
-                               0, stream, w, n, ws.hist, ws.nblocks, status);
-        else if (dig != nullptr)
-            hipLaunchKernelGGL(sort_hist_bytes_kernel<KPT>, dim3(ws.nblocks), dim3(kSortThreads),
-                               0, stream, dig, n, ws.hist, ws.nblocks);
+            hipLaunchKernelGGL((sort_first_hist_kernel<THREADS, KPT, FOLD>), dim3(ws.nblocks),
+                               dim3(THREADS), 0, stream, w, n, ws.hist, ws.nblocks, status);
+        else if (dig != nullptr) {
+            if constexpr (!FOLD)
+                hipLaunchKernelGGL(sort_hist_bytes_kernel<KPT>, dim3(ws.nblocks), dim3(kSortThreads),
+                                   0, stream, dig, n, ws.hist, ws.nblocks);
+        }
         else
-            hipLaunchKernelGGL(sort_hist_kernel<KPT>, dim3(ws.nblocks), dim3(kSortThreads), 0,
-                               stream, ws.keys[in], n, shift, ws.hist, ws.nblocks);
-        hipLaunchKernelGGL(digit_scan_kernel, dim3(256), dim3(1024), 0, stream, ws.hist,
+            hipLaunchKernelGGL((sort_hist_kernel<THREADS, KPT, FOLD>), dim3(ws.nblocks), dim3(THREADS),
+                               0, stream, ws.keys[in], n, shift, ws.hist, ws.nblocks);
+        if (!FOLD)
+            hipLaunchKernelGGL(digit_scan_kernel, dim3(256), dim3(1024), 0, stream, ws.hist,
                            ws.nblocks, ws.counts);
         uint8_t *const dnext = pass < 7 ? dig : nullptr;
         if (pass == 0)
-            hipLaunchKernelGGL((sort_scatter_kernel<KPT, true>), dim3(ws.nblocks),
-                               dim3(kSortThreads), pad, stream, nullptr, nullptr, w, T, payload_T,
+            hipLaunchKernelGGL((sort_scatter_kernel<THREADS, KPT, true, FOLD>), dim3(ws.nblocks),
+                               dim3(THREADS), pad, stream, nullptr, nullptr, w, T, payload_T,
                                n, shift, ws.hist, ws.counts, ws.nblocks, ws.keys[out],
                                ws.vals[out], dnext, status);
         else
-            hipLaunchKernelGGL((sort_scatter_kernel<KPT, false>), dim3(ws.nblocks),
-                               dim3(kSortThreads), pad, stream, ws.keys[in], ws.vals[in], nullptr,
+            hipLaunchKernelGGL((sort_scatter_kernel<THREADS, KPT, false, FOLD>), dim3(ws.nblocks),
+                               dim3(THREADS), pad, stream, ws.keys[in], ws.vals[in], nullptr,
                                nullptr, 0, n, shift, ws.hist, ws.counts, ws.nblocks, ws.keys[out],
                                ws.vals[out], dnext, status);
         err = hipGetLastError();
@@ -983,12 +1065,14 @@ static hipError_t launch_digit_passes(const double *w, const int32_t *T, int64_t
 static hipError_t launch_sort(const double *w, const int32_t *T, int64_t n, SortWs &ws,
                               int payload_T, int *status, hipStream_t stream)
 {
-    switch (ws.kpt) {
-    case 16: return launch_digit_passes<16>(w, T, n, ws, payload_T, status, stream);
-    case 8: return launch_digit_passes<8>(w, T, n, ws, payload_T, status, stream);
-    case 4: return launch_digit_passes<4>(w, T, n, ws, payload_T, status, stream);
-    default: return launch_digit_passes<2>(w, T, n, ws, payload_T, status, stream);
-    }
+    auto run = n > kFoldTo
+                   ? (ws.kpt == 16 ? launch_digit_passes<kSortThreads, 16, false>
+                                   : launch_digit_passes<kSortThreads, 8, false>)
+               : ws.threads == 256 ? launch_digit_passes<256, 2, true>
+               : ws.threads == 512 ? launch_digit_passes<512, 2, true>
+               : ws.kpt == 2       ? launch_digit_passes<1024, 2, true>
+                                   : launch_digit_passes<1024, 4, true>;
+    return run(w, T, n, ws, payload_T, status, stream);
 }
 
 hipError_t launch_sort_keys(const double *w, const int32_t *T, int64_t n, SortWs &ws, int *cur_out,
