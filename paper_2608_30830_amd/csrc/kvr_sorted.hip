@@ -405,6 +405,10 @@ __global__ void __launch_bounds__(THREADS) sort_scatter_kernel(
     if (!FOLD)
         my_off = static_cast<const uint32_t *>(offs)[(int64_t)threadIdx.x * nblocks + tile];
     for (int q = threadIdx.x; q < kWaves * 128; q += THREADS) reinterpret_cast<uint32_t *>(wcnt)[q] = 0;
+    uint32_t dbase = 0;   // keys with a digit below threadIdx.x
+    // before the keys' loads (after them: 1,622 against 1,610 us at 16.4M keys)
+    if (!FOLD) dbase = digit_exclusive_scan(totals[threadIdx.x]);
+    __syncthreads();
 
     const int64_t base = (int64_t)tile * kTile + (int64_t)wave * kWaveK;
     uint64_t key[KPT];
@@ -438,7 +442,6 @@ __global__ void __launch_bounds__(THREADS) sort_scatter_kernel(
             val[j] = i < n ? vals_in[i] : 0;
         }
     }
-    uint32_t dbase;   // keys with a digit below threadIdx.x
     if (FOLD) {
         __shared__ uint32_t part[2][kWaves][256];
         const Counts8 *h = static_cast<const Counts8 *>(offs);
@@ -462,8 +465,6 @@ __global__ void __launch_bounds__(THREADS) sort_scatter_kernel(
             total += my_off;
         }
         dbase = digit_exclusive_scan(total);
-    } else {
-        dbase = digit_exclusive_scan(totals[threadIdx.x]);   // its barriers also cover wcnt
     }
 #pragma unroll
     for (int j = 0; j < KPT; ++j) {
