@@ -415,7 +415,7 @@ int kvr::cost_grid_entry(const double *d_wait_s, const int32_t *d_ctx_tokens, in
         off_sort = off_a2 + align256(sizeof(double) * Lpad);
         // the same workspace with and without a requested order
         need = kvr::sort_ws_bytes(n);
-        if (kvr::bins_apply(P)) need = std::max(need, kvr::bin_ws_bytes(n, g->n_t1, P));
+        if (kvr::bins_apply(n, P, false)) need = std::max(need, kvr::bin_ws_bytes(n, g->n_t1, P));
         need += off_sort;
     }
     if (d_ws == nullptr) {
@@ -471,18 +471,20 @@ int kvr::cost_grid_entry(const double *d_wait_s, const int32_t *d_ctx_tokens, in
     }
     if ((rc = stage_tables(d_ws, off_t1, off_t2, off_a2, Lpad, *p, *g, s, tb)) != KVR_OK) return rc;
     KVR_MARK(g_prof_begin, s);
-    if (d_perm == nullptr && kvr::bins_apply(P)) {
+    kvr::SortWs sws{};
+    kvr::sort_ws_carve(at<char>(d_ws, off_sort), n, sws);
+    if (kvr::bins_apply(n, P, d_perm != nullptr)) {
         kvr::BinWs bws{};
         double last = g->t2[g->n_t2 - 1];
         if (std::isinf(last)) last = g->n_t2 > 1 ? g->t2[g->n_t2 - 2] : 0.0;
         kvr::bin_ws_carve(at<char>(d_ws, off_sort), n, g->n_t1, P,
                           std::fabs(g->t1[g->n_t1 - 1]) + last, bws);
         KVR_TRY(kvr::launch_binned(d_wait_s, d_ctx_tokens, n, tb, pr, bws, d_cost, status, s));
+        if (d_perm != nullptr)   // in the same area, after the costs
+            KVR_TRY(kvr::launch_sort_order(d_wait_s, d_ctx_tokens, n, sws, d_perm, status, s));
         KVR_MARK(g_prof_end, s);
         return KVR_OK;
     }
-    kvr::SortWs sws{};
-    kvr::sort_ws_carve(at<char>(d_ws, off_sort), n, sws);
     KVR_TRY(kvr::launch_sorted_path(d_wait_s, d_ctx_tokens, n, tb, pr, sws, d_cost, d_perm, status, s));
     KVR_MARK(g_prof_end, s);
     return KVR_OK;

@@ -62,9 +62,20 @@ static int64_t bin_chunk(int64_t n, int64_t bins)
     return c < kBinChunk ? c : kBinChunk;
 }
 
-// Policies up to which the bins replace the sort: nine ranges of bins at most, each of which
-// reads the sample once.
-bool bins_apply(int64_t P) { return P <= 16384; }
+// Whether the costs come from the bins: up to 16,384 policies (nine ranges of bins
+// at most, each of which reads the sample once).  With an order requested the scans
+// that the bins replace (with the last scatter's keys) are cheap until their gather
+// of the context sizes through the order leaves the caches, and the bins cost more
+// the more thresholds there are.  By the scans and by the bins, us: 2^20 waits and 65
+// policies 178 and 167, 544 policies 178 and 176, 1,025 policies 185 and 188; 2^21 waits
+// and 1,025 policies 245 and 228, 15,120 policies 257 and 313; 16.4M waits and 65
+// policies 1,612 and 1,104, 15,120 policies 1,639 and 1,584.
+constexpr int64_t kOrderBinsFrom = int64_t(1) << 20;
+
+bool bins_apply(int64_t n, int64_t P, bool order)
+{
+    return P <= 16384 && (!order || (n >= kOrderBinsFrom && P <= n / 2048));
+}
 
 // Global copies of each bin, block q of the sums adding into copy q % copies:
 // with one copy the atomics of 512 blocks on the same few addresses took 28 us

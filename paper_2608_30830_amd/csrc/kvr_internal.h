@@ -193,7 +193,7 @@ struct BinWs {
 size_t bin_ws_bytes(int64_t n, int64_t K1, int64_t P);
 // largest: the largest finite deadline of the grid, or any time of its scale.
 void bin_ws_carve(void *base, int64_t n, int64_t K1, int64_t P, double largest, BinWs &ws);
-bool bins_apply(int64_t P);
+bool bins_apply(int64_t n, int64_t P, bool order);
 hipError_t launch_binned(const double *w, const int32_t *T, int64_t n, const Tables &tb,
                          const PriceDev &pr, const BinWs &ws, double *cost_out, int *status,
                          hipStream_t stream);
@@ -220,6 +220,9 @@ void sort_ws_carve(void *base, int64_t n, SortWs &ws);
 // sorted position.
 hipError_t launch_sort_keys(const double *w, const int32_t *T, int64_t n, SortWs &ws, int *cur_out,
                             int *status, hipStream_t stream);
+// The order alone (n beyond one block's sort), straight to perm_out.
+hipError_t launch_sort_order(const double *w, const int32_t *T, int64_t n, SortWs &ws,
+                             int32_t *perm_out, int *status, hipStream_t stream);
 hipError_t launch_sorted_path(const double *w, const int32_t *T, int64_t n, const Tables &tb,
                               const PriceDev &pr, SortWs &ws, double *cost_out,
                               int32_t *perm_out, int *status, hipStream_t stream);

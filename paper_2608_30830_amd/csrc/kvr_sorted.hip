@@ -526,7 +526,7 @@ __global__ void __launch_bounds__(THREADS) sort_scatter_kernel(
             const uint64_t k = lkey[pos];
             const int64_t dest = (int64_t)gbase[(k >> shift) & 255u] + pos;
             if (dest >= 0 && dest < n) {  // always true when the histograms agree
-                keys_out[dest] = k;
+                if (keys_out != nullptr) keys_out[dest] = k;   // uniform
                 vals_out[dest] = lval[pos];
                 if (!FOLD && dig_out != nullptr)   // uniform
                     dig_out[dest] = (uint8_t)(k >> (shift + 8));
@@ -1013,7 +1013,8 @@ static size_t scatter_lds_pad(int kpt, int64_t n)
 
 template <int THREADS, int KPT, bool FOLD>
 static hipError_t launch_digit_passes(const double *w, const int32_t *T, int64_t n, SortWs &ws,
-                                      int payload_T, int *status, hipStream_t stream)
+                                      int payload_T, int32_t *order, int *status,
+                                      hipStream_t stream)
 {
     // From 2^22 keys each scatter also writes the next pass's digit bytes, to
     // the prefix-sum buffer (unused until the sort is done; 8 n bytes hold the
@@ -1055,16 +1056,18 @@ static hipError_t launch_digit_passes(const double *w, const int32_t *T, int64_t
         else
             hipLaunchKernelGGL((sort_scatter_kernel<THREADS, KPT, false, FOLD>), dim3(ws.nblocks),
                                dim3(THREADS), pad, stream, ws.keys[in], ws.vals[in], nullptr,
-                               nullptr, 0, n, shift, ws.hist, ws.counts, ws.nblocks, ws.keys[out],
-                               ws.vals[out], dnext, status);
+                               nullptr, 0, n, shift, ws.hist, ws.counts, ws.nblocks,
+                               pass == 7 && order != nullptr ? nullptr : ws.keys[out],
+                               pass == 7 && order != nullptr ? order : ws.vals[out], dnext, status);
         err = hipGetLastError();
     }
     return err;
 }
 
-// Eight passes leave the result in buffer 0.
+// Eight passes leave the result in buffer 0, or, with order, the payload there and
+// the keys nowhere.
 static hipError_t launch_sort(const double *w, const int32_t *T, int64_t n, SortWs &ws,
-                              int payload_T, int *status, hipStream_t stream)
+                              int payload_T, int32_t *order, int *status, hipStream_t stream)
 {
     auto run = n > kFoldTo
                    ? (ws.kpt == 16 ? launch_digit_passes<kSortThreads, 16, false>
@@ -1073,7 +1076,7 @@ static hipError_t launch_sort(const double *w, const int32_t *T, int64_t n, Sort
                : ws.threads == 512 ? launch_digit_passes<512, 2, true>
                : ws.kpt == 2       ? launch_digit_passes<1024, 2, true>
                                    : launch_digit_passes<1024, 4, true>;
-    return run(w, T, n, ws, payload_T, status, stream);
+    return run(w, T, n, ws, payload_T, order, status, stream);
 }
 
 hipError_t launch_sort_keys(const double *w, const int32_t *T, int64_t n, SortWs &ws, int *cur_out,
@@ -1085,7 +1088,14 @@ hipError_t launch_sort_keys(const double *w, const int32_t *T, int64_t n, SortWs
                            ws.keys[0], ws.vals[0], nullptr, nullptr, nullptr, status);
         return hipGetLastError();
     }
-    return launch_sort(w, T, n, ws, 0, status, stream);
+    return launch_sort(w, T, n, ws, 0, nullptr, status, stream);
+}
+
+hipError_t launch_sort_order(const double *w, const int32_t *T, int64_t n, SortWs &ws,
+                             int32_t *perm_out, int *status, hipStream_t stream)
+{
+    if (n <= kSortTile) return hipErrorInvalidValue;
+    return launch_sort(w, T, n, ws, 0, perm_out, status, stream);
 }
 
 hipError_t launch_sorted_path(const double *w, const int32_t *T, int64_t n, const Tables &tb,
@@ -1102,7 +1112,7 @@ hipError_t launch_sorted_path(const double *w, const int32_t *T, int64_t n, cons
     // without a requested order the payload is the context size itself, so the
     // scans read it in sorted order instead of gathering it through the order
     const bool want_perm = perm_out != nullptr;
-    hipError_t err = launch_sort(w, T, n, ws, want_perm ? 0 : 1, status, stream);
+    hipError_t err = launch_sort(w, T, n, ws, want_perm ? 0 : 1, nullptr, status, stream);
     if (err != hipSuccess) return err;
     int32_t *Tsorted = want_perm ? ws.vals[1] : ws.vals[0];   // buffer 1 is free after the sort
     if (want_perm)
