@@ -31,6 +31,8 @@
 #include "kvr_device.h"
 #include "kvr_dpp.h"
 
+#include <math.h>
+
 namespace kvr {
 
 constexpr int kReplayMaxN = 8192;
@@ -51,12 +53,13 @@ __device__ __forceinline__ bool valid_time(double x)
 }
 
 // Bucket of instant x among nb equal parts of the row's arrivals: a monotone
-// function of x (each step rounds monotonically), clamped to 0 .. nb - 1.
+// function of x (each step rounds monotonically), clamped to 0 .. nb - 1 before
+// it becomes an integer.  No NaN: a0 is finite, so x - a0 is none for a departure
+// that overflowed to infinity, and the scale is positive.
 __device__ __forceinline__ int time_bucket(double x, double a0, double scale, int nb)
 {
-    const double t = (x - a0) * scale;
-    const int b = t < (double)(nb - 1) ? (int)t : nb - 1;
-    return b < 0 ? 0 : b;
+    const double t = fmin((x - a0) * scale, (double)(nb - 1));
+    return (int)fmax(t, 0.0);
 }
 
 // For every request j of a row (n <= MAXN) and timer k the packed word
@@ -114,7 +117,9 @@ __attribute__((amdgpu_waves_per_eu(MAXN <= 4096 ? 6 : 4))) replay_release_kernel
         __syncthreads();
         const double a0 = A[0], span = A[n - 1] - a0;
         double scale = (double)kBuckets / span;
-        if (!(span > 0.0) || !(scale <= 1.7976931348623157e308)) scale = 0.0;   // one bucket
+        // no span, or one so small that its scale overflows: every arrival in bucket 0
+        // (a scale of 0 would make an infinite departure inf * 0)
+        if (!(span > 0.0) || !(scale <= 1.7976931348623157e308)) scale = 2.2250738585072014e-308;
         for (int j = t; j < n; j += kThreads) {
             const double aj = A[j], before = j > 0 ? A[j - 1] : aj;
             if (!(before <= aj)) bad = true;   // arrivals must not decrease

@@ -149,6 +149,9 @@ def _odd_rows(shape, n, rng):
     elif shape == "huge":                # departures overflow to infinity
         arr = np.linspace(0.0, 1.7e308, n)
         w = np.where(rng.random(n) < 0.5, 1.0e308, w)
+    elif shape == "huge_instant":        # no span, and departures that overflow
+        arr = np.full(n, 1.7e308)
+        w = np.where(rng.random(n) < 0.5, 1.0e308, w)
     elif shape == "chains":              # every request released at one of the next few arrivals
         arr = np.arange(n) * 1.0
         w = rng.integers(0, 4, n) * 1.0
@@ -157,8 +160,8 @@ def _odd_rows(shape, n, rng):
     return arr, w
 
 
-@pytest.mark.parametrize("shape", ["one_instant", "two_bursts", "denormal_span", "huge", "chains",
-                                   "ragged"])
+@pytest.mark.parametrize("shape", ["one_instant", "two_bursts", "denormal_span", "huge",
+                                   "huge_instant", "chains", "ragged"])
 @pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 1024, 1025, 4096, 4097])
 def test_replay_odd_rows(kvr, oracle_mod, shape, n):
     rng = np.random.Generator(np.random.PCG64(n))
@@ -166,4 +169,4 @@ def test_replay_odd_rows(kvr, oracle_mod, shape, n):
     arr, w = np.stack([r[0] for r in rows]), np.stack([r[1] for r in rows])
     T = rng.integers(1, 50, (2, n)).astype(np.int32)
     for c2 in (1, 5, 64, n + 7):
-        _check(kvr, oracle_mod, arr, w, [2.0, 33.0, math.inf], c2, T)
+        _check(kvr, oracle_mod, arr, w, [2.0, 33.0, 5.0e307, math.inf], c2, T)
