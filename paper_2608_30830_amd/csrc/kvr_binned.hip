@@ -126,6 +126,14 @@ __device__ __forceinline__ double fixed_edge(int q)
     return __longlong_as_double((long long)bits);
 }
 
+// Biased exponent of a bin's width, whose sums count units of 2^(it - 1022 - 64).  From
+// 12 down that unit is 2^-1074, of which every binary64 number is a multiple.
+__device__ __forceinline__ int bin_scale(double width)
+{
+    const int e = (int)((uint64_t)__double_as_longlong(width) >> 52);
+    return e > 12 ? e : 12;
+}
+
 // Item i < K1 is timer t1[i], item K1 + f policy f's deadline, the rest the
 // fixed edges.  The bin of a timer or a deadline (the thresholds strictly
 // below it) goes to at[i]; the thresholds in order to
@@ -293,12 +301,10 @@ __global__ void __launch_bounds__(kBinThreads) bin_sums_kernel(const double *__r
             atomicAdd(&sumT[pos[u]], (unsigned long long)t[u]);
             double base = edge[pos[u]];
             base = base > 0.0 ? base : 0.0;
-            // width < 2^(e - 1022): (w - base) * 2^(32 - (e - 1022)) < 2^32.
-            // (A width below 2^-958 takes the scale of 2^-958.)
-            const uint32_t e = (uint32_t)((uint64_t)__double_as_longlong(top - base) >> 52);
-            const uint32_t es = e > 64u ? e : 64u;
-            const double d = (x[u] - base) *
-                             __longlong_as_double((long long)((uint64_t)(2077u - es) << 52));
+            // width < 2^(e - 1022): (w - base) * 2^(32 - (e - 1022)) < 2^32, by an
+            // exponent add (the power itself overflows for widths below 2^-991)
+            const int es = bin_scale(top - base);
+            const double d = ldexp(x[u] - base, 1054 - es);
             const uint32_t dh = (uint32_t)d;
             const uint32_t dl = (uint32_t)((d - (double)dh) * 4294967296.0);
             const uint64_t p0 = (uint64_t)(uint32_t)t[u] * dl;
@@ -354,8 +360,7 @@ __device__ __forceinline__ void bin_prefix(const BinWs &ws, int first, int end, 
             S = 0.0;
             return;
         }
-        const uint32_t e = (uint32_t)((uint64_t)__double_as_longlong(top - base) >> 52);
-        const int es = (int)(e > 64u ? e : 64u);
+        const int es = bin_scale(top - base);
         // the limbs count units of 2^(es - 1022 - 64)
         const double frac = (double)in[1] + ldexp((double)in[2] + ldexp((double)in[3], 47), 47);
         S = fma(base, (double)N, ldexp(frac, es - 1022 - 64));

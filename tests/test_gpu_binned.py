@@ -8,7 +8,8 @@ Tolerance: the per-bin sums are exact up to 2^-64 of a bin's width per wait; the
 prefix sums over M + 1 bins add at most ceil((M + 1) / 1024) terms in a thread
 and a 10-level tree, so with the closed form's own dozen roundings every cost
 is within 64 * 2^-53 (M + 1 <= 32 * 1024) of the sum of its terms' magnitudes:
-(a1 t1 + a2 min(e, max w) + b2 + b3) * tokens / n, doubled for the terms that are
+(a1 t1 + a2 min(e, max w) + b2 + b3) * tokens / n (the last three only for
+timers that some wait passes), doubled for the terms that are
 differences of two prefix sums."""
 import numpy as np
 import pytest
@@ -34,8 +35,12 @@ def _bound(pr, wl):
     wmax = wl.wait_s.max()
     e = np.minimum(wl.t1[:, None] + wl.t2[None, :], wmax)
     t1 = np.minimum(wl.t1, wmax)
-    per = (pr.a1 * t1[None, :, None] + a2[:, None, None] * (e + t1[:, None])[None] + pr.b2 + pr.b3)
-    return 2.0 * 64.0 * H.EPS * per * float(wl.ctx_tokens.astype(np.float64).sum()) / wl.n
+    # past the longest wait no request pays a host term: exact zeros, not differences
+    host = (a2[:, None, None] * (e + t1[:, None])[None] + pr.b2 + pr.b3) * (wl.t1 < wmax)[None, :, None]
+    per = pr.a1 * t1[None, :, None] + host
+    # a few roundings to multiples of the smallest denormal, where the costs are that small
+    return (2.0 * 64.0 * H.EPS * per * float(wl.ctx_tokens.astype(np.float64).sum()) / wl.n
+            + 4 * 5e-324)
 
 
 def _check(kvr, oracle_mod, wl):
@@ -74,7 +79,8 @@ def test_beyond_the_limit_still_sorts(kvr, oracle_mod):
 
 
 @pytest.mark.parametrize("shape", ["crowded", "heavy", "beyond", "equal_rows", "infinite_rows",
-                                   "tiny_widths", "far_below", "no_inf"])
+                                   "tiny_widths", "far_below", "tiny_waits",
+                                   "denormal_waits", "no_inf"])
 def test_extreme_samples(kvr, oracle_mod, shape):
     rng = np.random.Generator(np.random.PCG64(9))
     wl = workloads.random_case(47, 70001, 3, 40, 4, ties=True, inf_last=shape != "no_inf")
@@ -99,6 +105,15 @@ def test_extreme_samples(kvr, oracle_mod, shape):
         wl.wait_s[:1000] = rng.integers(0, 6, 1000) * 5e-324
     elif shape == "far_below":           # waits many binades below every timer
         wl.wait_s = 10.0 ** rng.uniform(-300.0, -30.0, wl.n)
+    elif shape in ("tiny_waits", "denormal_waits"):
+        # prices at which T*w decides the costs although every wait is far below
+        # 2^-958 s: no holding price, resume prices of the size of alpha_1 * w
+        unit = 1e-300 if shape == "tiny_waits" else 1e-320
+        wl.wait_s = unit * (0.5 + rng.random(wl.n))
+        wl.t1 = np.array([0.0, 0.8 * unit, 1.0])
+        wl.lam = np.array([0.1, 0.2])
+        wl.platform = dict(wl.platform, hbm_usable_bytes=wl.kv_bytes_per_token,
+                           host_link_bytes_per_s=1e304, prefill_tokens_per_s=1e300)
     _check(kvr, oracle_mod, wl)
 
 
