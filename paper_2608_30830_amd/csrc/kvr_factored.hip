@@ -396,7 +396,12 @@ __global__ void __launch_bounds__(kFPThreads) factored_prefix_kernel(
 //
 // A wrapped counter is found as above (the decoded total differs from m); the
 // resample is then counted again by sorted position with 32-bit counters,
-// kFLdsWords positions per pass.
+// kFLdsWords positions per pass.  At m = 4 n and n = 65,536 about a quarter of the
+// rows wrap, from m = 8 n practically all.  The recount is bound by the latency, and
+// with four blocks to a CU by the rate, of its gathers of the ranks, 4 or 16 of them
+// in flight per thread: 256 rows of 4 n, 8 n and 16 n draws 1.49, 4.32 and 8.45 ms per
+// call (factored_prefix_kernel 2.44, 5.61 and 11.05; one draw at a time 3.44,
+// 9.31 and 18.47).
 constexpr int kFStage = 108;   // records per wave: four blocks of 39.5 KiB per CU
 
 __global__ void __launch_bounds__(kFPThreads) factored_prefix_small_kernel(
@@ -522,43 +527,52 @@ __global__ void __launch_bounds__(kFPThreads) factored_prefix_small_kernel(
 
     for (int x = t; x < kFLdsWords; x += kFPThreads) lh[x] = 0u;
     __syncthreads();
-    uint32_t most = 0;   // the largest index met, as unsigned
-    auto draw = [&](int32_t ii) {
-        const uint32_t i = (uint32_t)ii;
-        most = most > i ? most : i;
-        // a bad index counts somewhere in the table
-        uint32_t *word = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(lh) + ((i >> 1) & 0x7ffcu));
-        atomicAdd(word, 1u << ((i << 2) & 31u));
-    };
+    // every draw of the row, read 16 bytes a lane from the first aligned one on, kQ
+    // reads in flight: take(d) gets an array of 1, 4 or 4 kQ of them
     const int head_all = (int)((16u - ((uint32_t)(uintptr_t)row & 15u)) & 15u) / 4;   // to 16-byte alignment
     const int head = head_all < m ? head_all : m;
     const int quads = (m - head) / 4;
-    if (t < head) draw(row[t]);
-    {
+    auto each_draw = [&](auto take) {
+        constexpr int kQ = 4;
         const int4 *v = reinterpret_cast<const int4 *>(row + head);
-        constexpr int kQ = 4;   // loads of four draws in flight
+        auto one = [&](int j) {
+            const int32_t d[1] = {row[j]};
+            take(d);
+        };
+        if (t < head) one(t);
         int q = t;
         for (; q + (kQ - 1) * kFPThreads < quads; q += kQ * kFPThreads) {
-            int4 d[kQ];
+            int4 x[kQ];
+            int32_t d[4 * kQ];
 #pragma unroll
-            for (int u = 0; u < kQ; ++u) d[u] = v[q + u * kFPThreads];
+            for (int u = 0; u < kQ; ++u) x[u] = v[q + u * kFPThreads];
 #pragma unroll
             for (int u = 0; u < kQ; ++u) {
-                draw(d[u].x);
-                draw(d[u].y);
-                draw(d[u].z);
-                draw(d[u].w);
+                d[4 * u] = x[u].x;
+                d[4 * u + 1] = x[u].y;
+                d[4 * u + 2] = x[u].z;
+                d[4 * u + 3] = x[u].w;
             }
+            take(d);
         }
         for (; q < quads; q += kFPThreads) {
-            const int4 d = v[q];
-            draw(d.x);
-            draw(d.y);
-            draw(d.z);
-            draw(d.w);
+            const int4 x = v[q];
+            const int32_t d[4] = {x.x, x.y, x.z, x.w};
+            take(d);
         }
-    }
-    for (int j = head + 4 * quads + t; j < m; j += kFPThreads) draw(row[j]);
+        for (int j = head + 4 * quads + t; j < m; j += kFPThreads) one(j);
+    };
+    uint32_t most = 0;   // the largest index met, as unsigned
+    each_draw([&](const auto &d) {
+#pragma unroll
+        for (int u = 0; u < (int)(sizeof(d) / sizeof(d[0])); ++u) {
+            const uint32_t i = (uint32_t)d[u];
+            most = most > i ? most : i;
+            // a bad index counts somewhere in the table
+            uint32_t *word = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(lh) + ((i >> 1) & 0x7ffcu));
+            atomicAdd(word, 1u << ((i << 2) & 31u));
+        }
+    });
     if (most >= (uint32_t)n) flag_domain(status);
     __syncthreads();
     int decoded = 0;
@@ -584,11 +598,16 @@ __global__ void __launch_bounds__(kFPThreads) factored_prefix_small_kernel(
             __syncthreads();
             for (int x = t; x < kFLdsWords; x += kFPThreads) lh[x] = 0u;
             __syncthreads();
-            for (int j = t; j < m; j += kFPThreads) {
-                const int32_t ii = row[j];
-                const int k = rank[(uint32_t)ii < (uint32_t)n ? ii : 0] - p0;
-                if ((uint32_t)k < (uint32_t)(p1 - p0)) atomicAdd(&lh[k], 1u);
-            }
+            each_draw([&](const auto &d) {
+                constexpr int nd = (int)(sizeof(d) / sizeof(d[0]));
+                int32_t k[nd];
+#pragma unroll
+                for (int u = 0; u < nd; ++u)   // the ranks in flight together
+                    k[u] = rank[(uint32_t)d[u] < (uint32_t)n ? d[u] : 0] - p0;
+#pragma unroll
+                for (int u = 0; u < nd; ++u)
+                    if ((uint32_t)k[u] < (uint32_t)(p1 - p0)) atomicAdd(&lh[k[u]], 1u);
+            });
             __syncthreads();
             scan(p0, p1, [&](int k, uint32_t) { return lh[k - p0]; });
         }

@@ -288,3 +288,29 @@ def test_factored_small_edges(kvr, oracle_mod, case):
         assert_costs(bc[r], rbc)
     best2, bc2 = (_np(x) for x in _factored(kvr, wl))
     assert np.array_equal(best2, best) and np.array_equal(bc2, bc)
+
+
+@pytest.mark.parametrize("n,m", [(5, 16), (100, 255), (8191, 2047), (8192, 2048), (8193, 2049),
+                                 (16385, 4097), (65535, 6145), (65536, 300000)])
+def test_factored_recount_edges(kvr, oracle_mod, n, m):
+    """Rows that wrap a 4-bit counter and are counted again with 32-bit ones, around
+    the recount's range of sorted positions (8,192) and its step of 2,048 draws:
+    one sample drawn m times, random rows with one sample drawn 16 times (at their
+    start, so that full and ragged steps hold it), a row that draws the last sorted
+    position only.  Costs and selections against the oracle's closed form of the row,
+    within the tolerances of the other factored tests."""
+    wl = workloads.random_case(230, n, 3, 31, 5, resamples=4, m=m, ties=True)
+    order = np.argsort(wl.wait_s, kind="stable")
+    wl.idx[0, :] = order[n // 2]
+    wl.idx[1, :16] = order[0]
+    wl.idx[2, :] = order[n - 1]
+    wl.idx[3, -16:] = order[min(n - 1, 8192)]
+    best, bc, cost = (_np(x) for x in _factored(kvr, wl, want_cost=True))
+    pr = oracle_mod.workload_prices(wl)
+    for r in range(4):
+        ref = oracle_mod.closed_form_grid(wl.wait_s, wl.ctx_tokens, pr, wl.t1, wl.t2, wl.lam,
+                                          idx_row=wl.idx[r])
+        assert_costs(cost[r], ref)
+        rb, rbc, _ = oracle_mod.select(ref, wl.t2)
+        assert_selection(ref, best[r], rb)
+        assert_costs(bc[r], rbc)
