@@ -246,21 +246,32 @@ __attribute__((amdgpu_waves_per_eu(MAXN <= 4096 ? 6 : 4))) replay_release_kernel
 // being made: they start out counted as admitted, and the scans are repeated
 // with the corrected counts until no such decision changes.  A decision depends
 // on earlier lanes only, so each round settles at least one more lane: at most
-// 65 rounds, usually one or two.
+// 65 rounds.  How many depends on the chains of requests that free a slot for the
+// next one within 64 arrivals, so on C2: for Poisson arrivals at one to three times
+// the critical load 1.0-2.8 on average at C2 = 425, 4-7 at 8, 9-14 at 2 (regular
+// patterns of arrivals and waits reach 33 at 2 to 4).  8,192 sequences x 4,000
+// requests x 5 timers take 0.58-0.63 ms per call at C2 = 425, 0.97-1.07 at 8 and
+// 1.78-1.85 at 2.
+//
+// ONE: with a single slot the admitted requests are a chain, each the arrival that
+// releases the one before, and everything between is refused; so the wave follows
+// the releases, a run of admissions of neighbouring arrivals at a time, without
+// counts.  At 0.1, 1 and 3 times the critical load that call takes 0.62, 1.12 and
+// 1.12 ms, by rounds (5 to 20 per 64 arrivals) 1.11, 2.67 and 2.68.
 //
 // Bound by the wave's instruction stream (about 100 VALU instructions and four
-// LDS accesses per 64 arrivals), 19 waves per CU by LDS at n = 4,000; the
+// LDS accesses per 64 arrivals and round), 19 waves per CU by LDS at n = 4,000; the
 // packed words are read four steps ahead.
-template <bool CTX>
+template <bool CTX, bool ONE>
 __global__ void __launch_bounds__(kWave) replay_admit_kernel(
     const int32_t *__restrict__ ctx, int64_t reps, int n, int64_t c2,
     const uint16_t *__restrict__ rel, double b2, double b3, double *__restrict__ cost,
     int64_t *__restrict__ restored_out, int64_t *__restrict__ admitted_out, int k0, int kn, int K)
 {
-    extern __shared__ uint32_t freed[];   // [64 * ceil(n / 64) / 2]
+    extern __shared__ uint32_t freed[];   // [64 * ceil(n / 64) / 2], none with ONE
     const int lane = threadIdx.x;
     const int steps = (n + kWave - 1) / kWave;
-    const int words = steps * (kWave / 2);
+    const int words = ONE ? 0 : steps * (kWave / 2);
     const int64_t pairs = reps * kn;
     // occupancy is at most n, so C2 above n is the same as n + 1
     const int cap = (c2 > (int64_t)n) ? n + 1 : (int)c2;
@@ -273,7 +284,32 @@ __global__ void __launch_bounds__(kWave) replay_admit_kernel(
         __syncthreads();
 
         int occ = 0, admitted = 0;      // uniform
+        int next = 0;                   // ONE: the next arrival that finds the slot free
         int64_t restored = 0, total = 0;
+        auto count = [&](bool adm, bool in, bool stays, int32_t T) {
+            admitted += __popcll(__ballot(adm));
+            if (CTX) {
+                T = T < 1 ? 1 : T;
+                total += in ? T : 0;
+                restored += adm && stays ? T : 0;
+            } else {
+                restored += __popcll(__ballot(adm && stays));
+            }
+        };
+        auto follow = [&](uint32_t x, int32_t T, int j0) {
+            const int end = j0 + kWave < n ? j0 + kWave : n, last = end - j0 - 1;
+            const int release = (int)(x & (kStaysBit - 1));   // later than its request
+            // where a run of admissions ends: the slot is not free again at the next arrival
+            const uint64_t stops = __ballot(release != j0 + lane + 1) | 1ull << last;
+            uint64_t chain = 0;
+            while (next < end) {
+                const int p = next - j0, q = p + __builtin_ctzll(stops >> p);   // q <= last
+                chain |= (~0ull >> (kWave - 1 - q)) & (~0ull << p);
+                const int f = __builtin_amdgcn_readlane(release, q);
+                next = f > j0 + q ? f : j0 + q + 1;
+            }
+            count(((chain >> lane) & 1u) != 0u, j0 + lane < n, (x & kStaysBit) != 0u, T);
+        };
         auto step = [&](uint32_t x, int32_t T, int j0) {
             const int j = j0 + lane;
             const bool in = j < n;
@@ -305,14 +341,7 @@ __global__ void __launch_bounds__(kWave) replay_admit_kernel(
                 __syncthreads();
             }
             occ += __builtin_amdgcn_readlane(s, kWave - 1) - __builtin_amdgcn_readlane(m, kWave - 1);
-            admitted += __popcll(__ballot(adm));
-            if (CTX) {
-                T = T < 1 ? 1 : T;
-                total += in ? T : 0;
-                restored += adm && stays ? T : 0;
-            } else {
-                restored += __popcll(__ballot(adm && stays));
-            }
+            count(adm, in, stays, T);
             if (adm && !inner && f < n) atomicAdd(word, one);
             __syncthreads();
         };
@@ -334,7 +363,8 @@ __global__ void __launch_bounds__(kWave) replay_admit_kernel(
                     const uint32_t xu = x[u];
                     const int32_t Tu = T[u];
                     fetch(u, j0 + kAhead * kWave);
-                    step(xu, Tu, j0);
+                    if constexpr (ONE) follow(xu, Tu, j0);
+                    else step(xu, Tu, j0);
                 }
             }
         }
@@ -410,13 +440,14 @@ hipError_t launch_replay(const double *arrival, const double *wait, const int32_
         if ((err = hipGetLastError()) != hipSuccess) break;
         const int64_t pairs = reps * kn;
         const unsigned blocks = pairs < kReplayMaxBlocks ? (unsigned)pairs : kReplayMaxBlocks;
-        const size_t lds = sizeof(uint16_t) * kWave * (size_t)((n + kWave - 1) / kWave);
-        if (ctx != nullptr)
-            hipLaunchKernelGGL(replay_admit_kernel<true>, dim3(blocks), dim3(kWave), lds, stream,
-                               ctx, reps, ni, c2, rel, b2, b3, cost, restored, admitted, k0, kn, K);
-        else
-            hipLaunchKernelGGL(replay_admit_kernel<false>, dim3(blocks), dim3(kWave), lds, stream,
-                               ctx, reps, ni, c2, rel, b2, b3, cost, restored, admitted, k0, kn, K);
+        // one slot is followed, more are counted (the kernel's comment has both measured)
+        const size_t lds = c2 == 1 ? 0 : sizeof(uint16_t) * kWave * (size_t)((n + kWave - 1) / kWave);
+        auto admit = c2 == 1 ? (ctx != nullptr ? replay_admit_kernel<true, true>
+                                               : replay_admit_kernel<false, true>)
+                             : (ctx != nullptr ? replay_admit_kernel<true, false>
+                                               : replay_admit_kernel<false, false>);
+        hipLaunchKernelGGL(admit, dim3(blocks), dim3(kWave), lds, stream, ctx, reps, ni, c2, rel,
+                           b2, b3, cost, restored, admitted, k0, kn, K);
         err = hipGetLastError();
     }
     return err;
