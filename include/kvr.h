@@ -149,9 +149,10 @@ int kvr_prices_from_platform(double kv_bytes_per_token, double hbm_usable_bytes,
  *                   KVR_SORTED: closed form per policy from the sums of T
  *                   and T*w over the waits at or below each timer and
  *                   deadline, by bins between the timers and deadlines, or
- *                   (beyond 16,384 policies, or with d_perm below 2^20 waits or
- *                   beyond n / 2,048 policies) by prefix sums over the sorted
- *                   waits; d_perm by a stable radix sort.
+ *                   (beyond 16,384 policies, or for at most 2,048 waits and
+ *                   more than 48 timers of each kind, or with d_perm below 2^20
+ *                   waits or beyond n / 2,048 policies) by prefix sums over the
+ *                   sorted waits; d_perm by a stable radix sort.
  *   d_cost          device, float64 [n_lam][n_t1][n_t2]: mean GPU-s per
  *                   request (written in full).
  *   d_perm          device, int32 [n] or NULL: KVR_SORTED only, the stable

@@ -415,7 +415,8 @@ int kvr::cost_grid_entry(const double *d_wait_s, const int32_t *d_ctx_tokens, in
         off_sort = off_a2 + align256(sizeof(double) * Lpad);
         // the same workspace with and without a requested order
         need = kvr::sort_ws_bytes(n);
-        if (kvr::bins_apply(n, P, false)) need = std::max(need, kvr::bin_ws_bytes(n, g->n_t1, P));
+        if (kvr::bins_apply(n, g->n_t1, g->n_t2, false))
+            need = std::max(need, kvr::bin_ws_bytes(n, g->n_t1, P));
         need += off_sort;
     }
     if (d_ws == nullptr) {
@@ -473,7 +474,7 @@ int kvr::cost_grid_entry(const double *d_wait_s, const int32_t *d_ctx_tokens, in
     KVR_MARK(g_prof_begin, s);
     kvr::SortWs sws{};
     kvr::sort_ws_carve(at<char>(d_ws, off_sort), n, sws);
-    if (kvr::bins_apply(n, P, d_perm != nullptr)) {
+    if (kvr::bins_apply(n, g->n_t1, g->n_t2, d_perm != nullptr)) {
         kvr::BinWs bws{};
         double last = g->t2[g->n_t2 - 1];
         if (std::isinf(last)) last = g->n_t2 > 1 ? g->t2[g->n_t2 - 2] : 0.0;

@@ -70,10 +70,20 @@ static int64_t bin_chunk(int64_t n, int64_t bins)
 // policies 178 and 167, 544 policies 178 and 176, 1,025 policies 185 and 188; 2^21 waits
 // and 1,025 policies 245 and 228, 15,120 policies 257 and 313; 16.4M waits and 65
 // policies 1,612 and 1,104, 15,120 policies 1,639 and 1,584.
+//
+// A sample that one block sorts (kvr_sorted.hip) costs less in order than the search of
+// the thresholds' own ranks along more than 48 rows of deadlines (columns, whichever are
+// fewer).  By the sort and by the bins, us: 100 waits and 64 x 64 policies 25.2 and 26.3,
+// 56 x 56 25.3 and 28.1, 128 x 128 29.5 and 37.4; 2,048 waits 29.1 and 29.5, 29.4 and
+// 31.1, 33.8 and 40.9; with 48 x 48 25.1 and 23.6, 28.8 and 25.6, with 16 x 1,024 33.6 and
+// 32.1, 38.3 and 34.4.
 constexpr int64_t kOrderBinsFrom = int64_t(1) << 20;
+constexpr int64_t kFewLines = 48;
 
-bool bins_apply(int64_t n, int64_t P, bool order)
+bool bins_apply(int64_t n, int64_t K1, int64_t K2, bool order)
 {
+    const int64_t P = K1 * K2;
+    if (n <= kOneBlockSort && (K1 < K2 ? K1 : K2) > kFewLines) return false;
     return P <= 16384 && (!order || (n >= kOrderBinsFrom && P <= n / 2048));
 }
 

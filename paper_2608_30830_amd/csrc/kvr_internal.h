@@ -14,6 +14,7 @@ constexpr int kStatusDomain = 1;   // value of the workspace status word on a do
 constexpr int kSmallWaves = 8;     // waves per block of the small-sample kernel
 constexpr int kSmallMaxGroupTiles = 4096;   // (group, load tile)s of one small-sample launch
 constexpr int kSmallBatchGroups = 8;        // split groups per batch in that launch
+constexpr int kOneBlockSort = 2048;         // waits that one block sorts
 
 // Where a call's samples come from: the base arrays, optionally through
 // bootstrap index rows idx[R][m].
@@ -193,7 +194,7 @@ struct BinWs {
 size_t bin_ws_bytes(int64_t n, int64_t K1, int64_t P);
 // largest: the largest finite deadline of the grid, or any time of its scale.
 void bin_ws_carve(void *base, int64_t n, int64_t K1, int64_t P, double largest, BinWs &ws);
-bool bins_apply(int64_t n, int64_t P, bool order);
+bool bins_apply(int64_t n, int64_t K1, int64_t K2, bool order);
 hipError_t launch_binned(const double *w, const int32_t *T, int64_t n, const Tables &tb,
                          const PriceDev &pr, const BinWs &ws, double *cost_out, int *status,
                          hipStream_t stream);

@@ -36,6 +36,7 @@ namespace kvr {
 constexpr int kSortThreads = 256;
 constexpr int kSortKPT = 8;                                   // keys per thread
 constexpr int kSortTile = kSortThreads * kSortKPT;            // 2048 keys per tile
+static_assert(kSortTile == kOneBlockSort, "sort_small_kernel holds one tile");
 constexpr int kScanThreads = 256;
 constexpr int kScanIPT = 8;
 constexpr int kScanTile = kScanThreads * kScanIPT;

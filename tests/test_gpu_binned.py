@@ -65,8 +65,15 @@ def _check(kvr, oracle_mod, wl):
                                    (1, 1836), (1, 3881), (1, 3882), (1, 3883), (1, 3884),
                                    (8, 1023), (64, 130), (130, 64), (300, 1), (16, 1024)])
 def test_threshold_counts(kvr, oracle_mod, k1, k2):
-    _check(kvr, oracle_mod, workloads.random_case(700 + k1 + k2, 1500, k1, k2, 3, ties=True,
+    _check(kvr, oracle_mod, workloads.random_case(700 + k1 + k2, 2500, k1, k2, 3, ties=True,
                                                      inf_last=k2 > 1))
+
+
+# one block sorts up to 2,048 waits, the cheaper way beyond 48 rows and columns of deadlines
+@pytest.mark.parametrize("n,k1,k2", [(1, 49, 49), (2048, 49, 49), (2049, 49, 49), (2048, 48, 51),
+                                     (2048, 51, 48), (1000, 49, 330), (1000, 330, 49)])
+def test_small_samples_of_many_rows(kvr, oracle_mod, n, k1, k2):
+    _check(kvr, oracle_mod, workloads.random_case(53 + n, n, k1, k2, 3, ties=n > 4))
 
 
 @pytest.mark.parametrize("n", [1, 2, 1023, 1024, 1025, 4097, 262144, 262145, 1048577])
