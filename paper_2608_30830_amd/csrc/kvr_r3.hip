@@ -32,6 +32,7 @@ constexpr int kR3BinsSmall = 2048;     // 16 KiB: grids with few deadlines
 constexpr int kR3Unroll = 4;           // draws per thread and step, fetched together
 constexpr int kR3LdsTable = 4096;      // timer-table entries staged in LDS (32 KiB)
 constexpr int64_t kR3ManyItems = 1 << 18;   // items whose own number fills the chip
+constexpr int64_t kR3ItemsPerLine = 1 << 14;
 
 // Number of grid deadlines fl(t1[a] + t2[k]) strictly below x, from timer
 // tables t1[K1] and t2[K2] (in LDS when they fit there), along the rows (or
@@ -268,8 +269,13 @@ hipError_t launch_r3(const SampleSrc &src, int64_t R, const Tables &tb, const R3
     const int64_t P = (int64_t)tb.K1 * tb.K2;
     // several histogram blocks per resample add into cleared rows
     const int64_t nzero = ws.nsplit > 1 ? R * ws.nbins : 0;
-    const int64_t items = src.n + P;
-    if ((tb.K1 < tb.K2 ? tb.K1 : tb.K2) < 4 || items > kR3ManyItems)
+    const int64_t items = src.n + P, lines = tb.K1 < tb.K2 ? tb.K1 : tb.K2;
+    // One lane an item with few lines to search, or with as many items as fill the chip,
+    // the fewer the shorter their chains.  Bootstraps of 16 rows x 500 draws by one lane
+    // and by eight, us: 4 lines and 50,000 samples 43.1 and 40.9, 100,000 43.6 and 43.5,
+    // 200,000 43.7 and 47.9; 9 lines and 150,000 50.6 and 49.5, 200,000 49.3 and 52.6;
+    // 16 lines and 250,000 64.3 and 55.9; 64 lines and 250,000 144 and 106.
+    if (lines < 4 || items > kR3ManyItems || items > kR3ItemsPerLine * lines)
         hipLaunchKernelGGL(r3_bins_kernel<1>, dim3((unsigned)((items + 255) / 256)), dim3(256), 0,
                            stream, src.w, src.T, src.n, tb, ws.rec, ws.lb, ws.S, nzero);
     else

@@ -301,3 +301,22 @@ def test_tall_grid_many_t1_timers(kvr, oracle_mod):
         assert_costs(_np(bc)[r], rbc)
     print(f"[tall] 2^21 policies, 500 waits: brute call {elapsed * 1e3:.1f} ms")
     assert elapsed < 5.0
+
+
+@pytest.mark.parametrize("k1,k2", [(3, 20), (4, 9), (9, 4), (16, 17), (17, 16)])
+@pytest.mark.parametrize("over", [0, 1])
+def test_deadline_bin_searches(kvr, oracle_mod, k1, k2, over):
+    """Base samples on both sides of the sizes at which an item's deadline search goes
+    from eight lanes to one (16,384 samples and policies per row of timers, at most
+    262,144; below four rows always one): bootstrap costs against the oracle."""
+    n = min(1 << 18, (1 << 14) * min(k1, k2)) - k1 * k2 + over
+    wl = workloads.random_case(431 + k1, n, k1, k2, 5, resamples=2, m=700, ties=True)
+    g = kvr.PolicyGrid(wl.t1, wl.t2, wl.lam)
+    best, _, cost = kvr.kvr_bootstrap(_dev(wl.wait_s, _f64()), _dev(wl.ctx_tokens, _i32()),
+                                      _dev(wl.idx, _i32()), _lib_prices(kvr, wl), g, want_cost=True)
+    pr = oracle_mod.workload_prices(wl)
+    for r in range(2):
+        ref = oracle_mod.cost_grid(wl.wait_s, wl.ctx_tokens, pr, wl.t1, wl.t2, wl.lam,
+                                   idx_row=wl.idx[r])
+        assert_costs(_np(cost)[r], ref)
+        assert_selection(ref, _np(best)[r], oracle_mod.select(ref, wl.t2)[0])
