@@ -33,6 +33,8 @@
 #include "kvr_dpp.h"
 #include "kvr_factored.h"
 
+#include <type_traits>
+
 namespace kvr {
 
 constexpr int kFThreads = 1024;
@@ -706,7 +708,17 @@ __device__ __forceinline__ void wave_argmin_halves(double (&c)[kPolLoads], int32
 // the row by each thread 504 us; without the evaluation the gathers alone take
 // 309 us (67 million 16-byte records), and records fetched two chunks ahead
 // change nothing.
-template <int FL, int U>
+//
+// COST (kernels of their own: the store's registers would cost the others a wave per
+// SIMD, 986 -> 1,094 us for the two-tier call): the chunks run in the flat order of
+// the policies, whose costs are stored from the lines in LDS, 64 consecutive ones a
+// wave.  Stored as the lines are formed, from the windows of rows above, in runs
+// of as few as 16 policies, most cache lines were written in two parts: 64 x 257
+// policies, 16 loads and 512 rows (1.08 GB) took 757 us per call and 414 now (one thread a
+// policy in flat order, the form before the lines, 416), 37 rows with 32 loads 377
+// and 250 (320), 1,024 rows of 16 x 100 policies with 32 loads 188 and 141 (161).
+// With chunks that meet in the middle of a line the first took 449.
+template <int FL, int U, bool COST>
 __global__ void __launch_bounds__(kFPolThreads *FL / kPolLoads) factored_policy_kernel(
     const double2 *__restrict__ TQ, int64_t nqs,
     const unsigned long long *__restrict__ totN, int64_t m, int64_t r0, int ntl, Tables tb,
@@ -723,6 +735,7 @@ __global__ void __launch_bounds__(kFPolThreads *FL / kPolLoads) factored_policy_
     __shared__ PolicyRow rows_of[kFPolThreads];          // the chunk's t1 rows
     __shared__ double rc[nw][FL];
     __shared__ int32_t rf[nw][FL];
+    __shared__ double la2[COST ? FL : 1];                // the tile's loads
     const int64_t rb = blockIdx.x / ntl;
     const int tile = (int)(blockIdx.x % ntl);
     const int64_t r = r0 + rb;
@@ -744,10 +757,24 @@ __global__ void __launch_bounds__(kFPolThreads *FL / kPolLoads) factored_policy_
         bc[l] = INFINITY;
         bf[l] = -1;
     }
-    const int cp = 1 << lcp, rp = kFPolThreads >> lcp;     // groups of a row per chunk, rows
     const int gpr = (tb.K2 + U - 1) / U;                   // groups of a row
-    const int ncol = (gpr + cp - 1) >> lcp, nchunk = ncol * ((tb.K1 + rp - 1) / rp);
-    const int my_row = g >> lcp, my_col = g & (cp - 1);    // of the group evaluated
+    const int cp = 1 << lcp;                               // groups of a row per chunk
+    // t1 rows per chunk (COST: at most)
+    const int rp = COST ? min(kFPolThreads, (kFPolThreads - 1) / gpr + 2) : kFPolThreads >> lcp;
+    // COST: a chunk begins again with the last groups (15 policies or more) of the one
+    // before, whose costs up to the next multiple of 16 that one stores
+    constexpr int kNext = kFPolThreads - (U > 1 ? 8 : 16);
+    const int nchunk = COST ? (max(tb.K1 * gpr - kFPolThreads, 0) + kNext - 1) / kNext + 1
+                            : ((gpr + cp - 1) >> lcp) * ((tb.K1 + rp - 1) / rp);
+    // row (from the chunk's first) and group in it of group x of a chunk that begins
+    // at group kg0 of a row
+    const float per_gpr = 1.0f / (float)gpr, per_row = 1.0f / (float)tb.K2;
+    auto place = [&](int kg0, int x) {
+        if (!COST) return make_int2(x >> lcp, kg0 + (x & (cp - 1)));
+        const int y = kg0 + x;   // below gpr + 256: at most one row on, or a quotient below 512
+        const int row = gpr > kFPolThreads ? (y >= gpr ? 1 : 0) : (int)(((float)y + 0.5f) * per_gpr);
+        return make_int2(row, y - row * gpr);
+    };
     // the kPer policies of a chunk whose lines this thread forms: policy
     // p = x kThreads + t of the chunk is number p % U of group p / U
     const bool forms = kPer > 1 || t < kChunkP;            // uniform per wave
@@ -762,9 +789,9 @@ __global__ void __launch_bounds__(kFPolThreads *FL / kPolLoads) factored_policy_
     auto slots = [&](int a0, int kg0) {
 #pragma unroll
         for (int x = 0; x < kPer; ++x) {
-            const int gx = group_of(x);
-            const int a = min(a0 + (gx >> lcp), tb.K1 - 1);
-            const int k = min((kg0 + (gx & (cp - 1))) * U + t % U, tb.K2 - 1);
+            const int2 at = place(kg0, group_of(x));
+            const int a = min(a0 + at.x, tb.K1 - 1);
+            const int k = min(at.y * U + t % U, tb.K2 - 1);
             slot[x] = (int32_t)min((uint32_t)ue[a * tb.K2 + k], last);   // P < 2^24
             t2[x] = tb.t2[k];
         }
@@ -779,17 +806,31 @@ __global__ void __launch_bounds__(kFPolThreads *FL / kPolLoads) factored_policy_
 #pragma unroll
         for (int x = 0; x < kPer; ++x) {
             const int gx = group_of(x);
-            const int a = a0 + (gx >> lcp), k = (kg0 + (gx & (cp - 1))) * U + t % U;
-            double2 ln = policy_line(rows_of[gx >> lcp], qe[x], t2[x], pr, tot);
+            const int2 at = place(kg0, gx);
+            const int a = a0 + at.x, k = at.y * U + t % U;
+            double2 ln = policy_line(rows_of[at.x], qe[x], t2[x], pr, tot);
             if (a >= tb.K1 || k >= tb.K2) ln = make_double2(INFINITY, 0.0);
-            else if (cost_out != nullptr)   // uniform
-                for (int l = 0; l < nl; ++l)
-                    cost_out[(r * tb.L + l0 + l) * P + (int64_t)a * tb.K2 + k] =
-                        fma(tb.a2[l0 + l], ln.y, ln.x) / md;
             lines[buf][t % U][gx] = ln;
         }
     };
+    // COST: a chunk's policies are consecutive; they are stored from a multiple of 16 to
+    // the next chunk's, 64 a wave: whole cache lines where the rows of costs are aligned
+    auto store_costs = [&](int a0, int kg0, int a1, int kg1, bool more, int buf) {
+        const int row0 = a0 * tb.K2, f0 = (row0 + kg0 * U + 15) & ~15;
+        const int f1 = more ? (a1 * tb.K2 + kg1 * U + 15) & ~15 : (int)P;
+        for (int f = f0 + t; f < f1; f += kThreads) {
+            // below K2 + 1,024: at most one row on, or a quotient below 2,048
+            const int y = f - row0;
+            const int row = tb.K2 > kChunkP ? (y >= tb.K2 ? 1 : 0) : (int)(((float)y + 0.5f) * per_row);
+            const int k = y - row * tb.K2;
+            const double2 ln = lines[buf][k % U][row * gpr + k / U - kg0];
+            double *out = cost_out + (r * tb.L + l0) * P + f;
+#pragma unroll 4
+            for (int l = 0; l < nl; ++l) out[l * P] = fma(la2[l], ln.y, ln.x) / md;
+        }
+    };
     static_assert(kThreads % U == 0, "a thread's policies have one place in their groups");
+    if (COST && t < FL) la2[t] = tb.a2[l0 + t];
     rows(0);
     if (forms) {
         slots(0, 0);
@@ -799,6 +840,12 @@ __global__ void __launch_bounds__(kFPolThreads *FL / kPolLoads) factored_policy_
     // the chunks run along the groups of a row, then to the next rows
     int a0 = 0, kg0 = 0;                        // chunk evaluated
     auto step = [&](int &a, int &kg) {
+        if (COST) {
+            kg += kNext;
+            a += kg / gpr;
+            kg %= gpr;
+            return;
+        }
         kg += cp;
         if (kg >= gpr) {
             kg = 0;
@@ -821,7 +868,8 @@ __global__ void __launch_bounds__(kFPolThreads *FL / kPolLoads) factored_policy_
 #pragma unroll
             for (int x = 0; x < kPer; ++x) qe[x] = qrow[slot[x]];
         }
-        const int a = a0 + my_row, kg = kg0 + my_col;
+        const int2 mine = place(kg0, g);                   // the group evaluated
+        const int a = a0 + mine.x, kg = mine.y;
         if (a < tb.K1 && kg < gpr) {
             double2 ln[U];
 #pragma unroll
@@ -839,8 +887,9 @@ __global__ void __launch_bounds__(kFPolThreads *FL / kPolLoads) factored_policy_
                 bf[l] = take ? id : bf[l];
             }
         }
+        if (COST) store_costs(a0, kg0, a1, kg1, more, cur);
         if (more) {
-            if (kg1 == 0) {   // the next chunk begins other t1 rows
+            if (COST || kg1 == 0) {   // the next chunk begins other t1 rows
                 rows(a1);
                 __syncthreads();
             }
@@ -977,20 +1026,15 @@ hipError_t launch_factored(const SampleSrc &src, int64_t R, const Tables &tb, co
                                ws.sort.vals[cur], ws.Ts, ws.sw, ws.qslot, ws.nqs, ws.TQ, ws.tot,
                                status);
         const dim3 gp((unsigned)(rb * ntl)), bp((unsigned)(kFPolThreads * FL / kPolLoads));
-        if (FL == 16 && U == 4)
-            hipLaunchKernelGGL((factored_policy_kernel<16, 4>), gp, bp, 0, stream, ws.TQ, ws.nqs,
-                               ws.tot, m, r0, ntl, tb, pr, ws.u1, ws.ue, lcp, best, best_cost, cost_out);
-        else if (FL == 16)
-            hipLaunchKernelGGL((factored_policy_kernel<16, 1>), gp, bp, 0, stream, ws.TQ, ws.nqs,
-                               ws.tot, m, r0, ntl, tb, pr, ws.u1, ws.ue, lcp, best, best_cost, cost_out);
-        else if (U == 4)
-            hipLaunchKernelGGL((factored_policy_kernel<kFLoads, 4>), gp, bp, 0, stream, ws.TQ,
-                               ws.nqs, ws.tot, m, r0, ntl, tb, pr, ws.u1, ws.ue, lcp, best,
-                               best_cost, cost_out);
-        else
-            hipLaunchKernelGGL((factored_policy_kernel<kFLoads, 1>), gp, bp, 0, stream, ws.TQ,
-                               ws.nqs, ws.tot, m, r0, ntl, tb, pr, ws.u1, ws.ue, lcp, best,
-                               best_cost, cost_out);
+        auto pick = [&](auto cost) {
+            constexpr bool C = decltype(cost)::value;
+            return FL == 16 ? (U == 4 ? factored_policy_kernel<16, 4, C> : factored_policy_kernel<16, 1, C>)
+                            : (U == 4 ? factored_policy_kernel<kFLoads, 4, C>
+                                      : factored_policy_kernel<kFLoads, 1, C>);
+        };
+        auto policy = cost_out != nullptr ? pick(std::true_type()) : pick(std::false_type());
+        hipLaunchKernelGGL(policy, gp, bp, 0, stream, ws.TQ, ws.nqs, ws.tot, m, r0, ntl, tb, pr,
+                           ws.u1, ws.ue, lcp, best, best_cost, cost_out);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
     return hipSuccess;
