@@ -33,6 +33,14 @@ constexpr int kR3Unroll = 4;           // draws per thread and step, fetched tog
 constexpr int kR3LdsTable = 4096;      // timer-table entries staged in LDS (32 KiB)
 constexpr int64_t kR3ManyItems = 1 << 18;   // items whose own number fills the chip
 constexpr int64_t kR3ItemsPerLine = 1 << 14;
+// Blocks of the item searches, four to a CU; beyond them (LOOP) they loop over the
+// items.  Blocks that start as others end leave the CUs filled unevenly for the grid
+// kernel, which counts on about four waves per SIMD: 220,521 waits, 143 x 16 policies and
+// 12 loads 463 us per call with a block for every 32 items, 392 with these.  Long searches
+// of many items want more waves than that: 2^24 waits and 40 x 40 policies 8.94 ms against
+// 9.35, 2^22 and 8 x 33 817 us against 834; with few rows 2^24 and 1 x 65 1,147 against 1,120.
+constexpr int64_t kR3BinsBlocks = 1024;
+constexpr int64_t kR3LoopItems = 1 << 20;
 
 // Number of grid deadlines fl(t1[a] + t2[k]) strictly below x, from timer
 // tables t1[K1] and t2[K2] (in LDS when they fit there), along the rows (or
@@ -57,7 +65,7 @@ __device__ int32_t deadlines_below(const double *t1v, int K1, const double *t2v,
 // NL lanes share an item's searches: one binary search after another along each
 // of min(K1, K2) rows is a chain of dependent reads (5,003 samples with nine rows:
 // 10.6 us by one lane, 5.0 by eight).  Also clears zero[0..nzero).
-template <int NL>
+template <int NL, bool LOOP>
 __global__ void __launch_bounds__(256) r3_bins_kernel(const double *__restrict__ w,
                                                       const int32_t *__restrict__ T, int64_t n,
                                                       Tables tb, SampleRec *__restrict__ rec,
@@ -78,7 +86,6 @@ __global__ void __launch_bounds__(256) r3_bins_kernel(const double *__restrict__
         t1v = lt;
         t2v = lt + tb.K1;
     }
-    const int64_t i = me / NL;
     const int lane = (int)(threadIdx.x % NL);
     auto below = [&](double x) {   // every lane of the item takes part
         int32_t c = deadlines_below(t1v, tb.K1, t2v, tb.K2, x, lane, NL);
@@ -86,23 +93,27 @@ __global__ void __launch_bounds__(256) r3_bins_kernel(const double *__restrict__
         return c;
     };
     const int64_t P = (int64_t)tb.K1 * tb.K2;
-    if (i < n) {
-        double x = w[i];
-        const uint64_t bits = (uint64_t)__double_as_longlong(x);
-        if (!(bits < 0x7ff0000000000000ull || bits == 0x8000000000000000ull)) x = 0.0;
-        int32_t t = T[i];
-        if (t < 1) t = 1;
-        SampleRec v;
-        v.bin = below(x + 0.0);
-        v.T = t;
-        v.w = x + 0.0;
-        if (lane == 0) rec[i] = v;
-    } else if (i - n < P) {
-        const int64_t f = i - n;
-        const int a = (int)(f / tb.K2), k = (int)(f % tb.K2);
-        const int32_t c = below(t1v[a] + t2v[k]);
-        if (lane == 0) lb[f] = c;
-    }
+    int64_t i = me / NL;
+    do {
+        if (i < n) {
+            double x = w[i];
+            const uint64_t bits = (uint64_t)__double_as_longlong(x);
+            if (!(bits < 0x7ff0000000000000ull || bits == 0x8000000000000000ull)) x = 0.0;
+            int32_t t = T[i];
+            if (t < 1) t = 1;
+            SampleRec v;
+            v.bin = below(x + 0.0);
+            v.T = t;
+            v.w = x + 0.0;
+            if (lane == 0) rec[i] = v;
+        } else if (i - n < P) {
+            const int64_t f = i - n;
+            const int a = (int)(f / tb.K2), k = (int)(f % tb.K2);
+            const int32_t c = below(t1v[a] + t2v[k]);
+            if (lane == 0) lb[f] = c;
+        }
+        i += (int64_t)gridDim.x * (blockDim.x / NL);
+    } while (LOOP && i < n + P);
 }
 
 // One block per (resample, split of its draws): histogram of T over the
@@ -275,12 +286,13 @@ hipError_t launch_r3(const SampleSrc &src, int64_t R, const Tables &tb, const R3
     // and by eight, us: 4 lines and 50,000 samples 43.1 and 40.9, 100,000 43.6 and 43.5,
     // 200,000 43.7 and 47.9; 9 lines and 150,000 50.6 and 49.5, 200,000 49.3 and 52.6;
     // 16 lines and 250,000 64.3 and 55.9; 64 lines and 250,000 144 and 106.
-    if (lines < 4 || items > kR3ManyItems || items > kR3ItemsPerLine * lines)
-        hipLaunchKernelGGL(r3_bins_kernel<1>, dim3((unsigned)((items + 255) / 256)), dim3(256), 0,
-                           stream, src.w, src.T, src.n, tb, ws.rec, ws.lb, ws.S, nzero);
-    else
-        hipLaunchKernelGGL(r3_bins_kernel<8>, dim3((unsigned)((items + 31) / 32)), dim3(256), 0,
-                           stream, src.w, src.T, src.n, tb, ws.rec, ws.lb, ws.S, nzero);
+    const bool one = lines < 4 || items > kR3ManyItems || items > kR3ItemsPerLine * lines;
+    const int64_t blocks = (items * (one ? 1 : 8) + 255) / 256;
+    const bool loop = blocks > kR3BinsBlocks && (lines < 8 || items <= kR3LoopItems);
+    auto bins = one ? (loop ? r3_bins_kernel<1, true> : r3_bins_kernel<1, false>)
+                    : (loop ? r3_bins_kernel<8, true> : r3_bins_kernel<8, false>);
+    hipLaunchKernelGGL(bins, dim3((unsigned)(loop ? kR3BinsBlocks : blocks)), dim3(256), 0, stream,
+                       src.w, src.T, src.n, tb, ws.rec, ws.lb, ws.S, nzero);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
     if (ws.nbins == 0) return hipSuccess;   // every deadline infinite: R3 = 0

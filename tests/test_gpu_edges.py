@@ -308,7 +308,8 @@ def test_tall_grid_many_t1_timers(kvr, oracle_mod):
 def test_deadline_bin_searches(kvr, oracle_mod, k1, k2, over):
     """Base samples on both sides of the sizes at which an item's deadline search goes
     from eight lanes to one (16,384 samples and policies per row of timers, at most
-    262,144; below four rows always one): bootstrap costs against the oracle."""
+    262,144; below four rows always one), where its blocks take several items a
+    thread: bootstrap costs against the oracle."""
     n = min(1 << 18, (1 << 14) * min(k1, k2)) - k1 * k2 + over
     wl = workloads.random_case(431 + k1, n, k1, k2, 5, resamples=2, m=700, ties=True)
     g = kvr.PolicyGrid(wl.t1, wl.t2, wl.lam)
@@ -320,3 +321,19 @@ def test_deadline_bin_searches(kvr, oracle_mod, k1, k2, over):
                                    idx_row=wl.idx[r])
         assert_costs(_np(cost)[r], ref)
         assert_selection(ref, _np(best)[r], oracle_mod.select(ref, wl.t2)[0])
+
+
+@pytest.mark.parametrize("n,k1,k2", [(32768 - 81, 9, 9), (32768 - 80, 9, 9), (262144 - 9, 3, 3),
+                                     (262145 - 9, 3, 3), ((1 << 20) - 81, 9, 9),
+                                     ((1 << 20) - 80, 9, 9)])
+def test_deadline_bin_loops(kvr, oracle_mod, n, k1, k2):
+    """Around the sizes at which the search's blocks begin to loop over the items (1,024
+    blocks of 32 or 256) and, with eight rows or more, stop to (2^20 items): costs of one
+    sample against the oracle's closed form."""
+    wl = workloads.random_case(437, n, k1, k2, 3, ties=True)
+    pr = oracle_mod.workload_prices(wl)
+    g = kvr.PolicyGrid(wl.t1, wl.t2, wl.lam)
+    cost = kvr.kvr_cost_grid(_dev(wl.wait_s, _f64()), _dev(wl.ctx_tokens, _i32()),
+                             _lib_prices(kvr, wl), g, method=kvr.KVR_BRUTE)
+    ref = oracle_mod.closed_form_grid(wl.wait_s, wl.ctx_tokens, pr, wl.t1, wl.t2, wl.lam)
+    assert_costs(_np(cost), ref)
