@@ -1001,13 +1001,18 @@ hipError_t launch_factored(const SampleSrc &src, int64_t R, const Tables &tb, co
                        dim3(256), 0, stream, ws.u1, ws.ue, tb.K1, P, n, ws.qbits, ws.qbase,
                        ws.qslot);
     if ((err = hipGetLastError()) != hipSuccess) return err;
-    const int FL = tb.L <= 16 ? 16 : kFLoads;                 // loads per policy block
-    const int ntl = (tb.L + FL - 1) / FL;
     // Groups of four host timers from where they fill a chunk on; fewer policies
     // keep a thread each (calls of 1,024 rows x 9,000 draws by U = 1 and 4: 1 x 257
     // policies 122.6 and 125.5 us, 4 x 257 127.1 and 131.1, 128 x 8 133.6 and 133.0,
     // 64 x 16 equal, 256 x 16 160.9 and 152.2, 512 x 8 166.1 and 157.4).
     const int U = tb.K2 >= 8 && P >= 4 * kFPolThreads ? 4 : 1;
+    // Loads per policy block: up to 16 take half a tile, except where costs are wanted of
+    // no more rows than CUs; there a block of 512 threads stores them faster (1, 64, 256
+    // and 300 rows of 64 x 257 policies and 16 loads 250, 256, 297 and 352 us; with 256
+    // threads 269, 274, 307 and 350).
+    const bool few = cost_out != nullptr && R <= 256 && U == 4;
+    const int FL = tb.L <= 16 && !few ? 16 : kFLoads;
+    const int ntl = (tb.L + FL - 1) / FL;
     const int lcp = policy_columns(tb.K1, (tb.K2 + U - 1) / U);
     for (int64_t r0 = 0; r0 < R; r0 += ws.Rb) {
         const int64_t rb = (R - r0 < ws.Rb) ? R - r0 : ws.Rb;

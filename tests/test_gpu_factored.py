@@ -319,16 +319,18 @@ def test_factored_recount_edges(kvr, oracle_mod, n, m):
 # chunks of 256 groups of one policy (below 1,024 policies, or rows of fewer than 8) or
 # four: one chunk and one more group, rows that leave one to three policies to their last
 # group, rows longer and shorter than a chunk, load tiles of 16 and 32 with a remainder
-@pytest.mark.parametrize("k1,k2,L", [(1, 1, 3), (1, 240, 16), (1, 256, 16), (1, 257, 17), (16, 16, 5),
-                                     (241, 1, 2), (300, 7, 33), (1, 1024, 16), (1, 1025, 5),
-                                     (114, 9, 32), (129, 8, 3), (61, 17, 7), (33, 34, 40),
-                                     (2, 1099, 31), (3, 2500, 2)])
-def test_factored_cost_chunks(kvr, oracle_mod, k1, k2, L):
+# (up to 256 rows a tile of 32 with four policies a group, whatever the loads)
+@pytest.mark.parametrize("k1,k2,L,rows", [
+    (1, 1, 3, 3), (1, 240, 16, 3), (1, 256, 16, 3), (1, 257, 17, 3), (16, 16, 5, 3),
+    (241, 1, 2, 3), (300, 7, 33, 3), (1, 1024, 16, 3), (1, 1025, 5, 3), (114, 9, 32, 3),
+    (129, 8, 3, 3), (61, 17, 7, 3), (33, 34, 40, 3), (2, 1099, 31, 3), (3, 2500, 2, 3),
+    (61, 17, 7, 257), (114, 9, 16, 257), (1, 1025, 3, 257)])
+def test_factored_cost_chunks(kvr, oracle_mod, k1, k2, L, rows):
     """The cost tensor, stored by chunks of policies, whole against the oracle's closed
     form (the tolerance of the other factored tests), nothing outside it, and the same
     selections as without it."""
     import torch
-    wl = workloads.random_case(240 + k1 % 7, 600, k1, k2, L, resamples=3, m=601, ties=True,
+    wl = workloads.random_case(240 + k1 % 7, 600, k1, k2, L, resamples=rows, m=601, ties=True,
                                inf_last=k2 > 1)
     g = kvr.PolicyGrid(wl.t1, wl.t2, wl.lam)
     call = kvr.BootstrapCall(_dev(wl.wait_s, _f64()), _dev(wl.ctx_tokens, _i32()),
@@ -341,10 +343,11 @@ def test_factored_cost_chunks(kvr, oracle_mod, k1, k2, L):
     assert call.status() == kvr.KVR_OK
     assert torch.all(padded[:32] == -7.0) and torch.all(padded[32 + size:] == -7.0)
     pr = oracle_mod.workload_prices(wl)
-    for r in range(3):
+    cost, picked = _np(call.cost), _np(call.best)
+    for r in (0, 1, rows - 1):
         ref = oracle_mod.closed_form_grid(wl.wait_s, wl.ctx_tokens, pr, wl.t1, wl.t2, wl.lam,
                                           idx_row=wl.idx[r])
-        assert_costs(_np(call.cost)[r], ref)
-        assert_selection(ref, _np(call.best)[r], oracle_mod.select(ref, wl.t2)[0])
+        assert_costs(cost[r], ref)
+        assert_selection(ref, picked[r], oracle_mod.select(ref, wl.t2)[0])
     best, bc = _factored(kvr, wl)
     assert torch.equal(best, call.best) and torch.equal(bc, call.best_cost)
