@@ -4,10 +4,12 @@ power of two that sizes the search and at the bin ranges, samples around the
 block and chunk sizes, waits on thresholds, equal and infinite thresholds,
 one crowded bin, the largest context sizes, and grids beyond the path's limit.
 
-Tolerance: the per-bin sums are exact up to 2^-64 of a bin's width per wait; the
-prefix sums over M + 1 bins add at most ceil((M + 1) / 1024) terms in a thread
-and a 10-level tree, so with the closed form's own dozen roundings every cost
-is within 64 * 2^-53 (M + 1 <= 32 * 1024) of the sum of its terms' magnitudes:
+Tolerance: the per-bin sums are exact up to 2^-64 of a bin's width per wait, and four
+roundings bring one to binary64.  A prefix sum passes it through at most 4 additions in a
+thread (4,096 bins), 6 in the wave's tree and 16 of wave totals, or, in tiles of 1,024
+bins, 1 + 6 + 16 and 33 of tile totals (32,980 bins at most): 60 roundings, 80 with the
+closed form's own, all of sums of terms of one sign.  So every cost is within 80 * 2^-53
+of the sum of its terms' magnitudes:
 (a1 t1 + a2 min(e, max w) + b2 + b3) * tokens / n (the last three only for
 timers that some wait passes), doubled for the terms that are
 differences of two prefix sums."""
@@ -33,13 +35,14 @@ def kvr():
 def _bound(pr, wl):
     a2 = np.maximum(0.0, wl.lam - pr.c2 / pr.w_ref) * pr.b3 / pr.c2
     wmax = wl.wait_s.max()
-    e = np.minimum(wl.t1[:, None] + wl.t2[None, :], wmax)
+    with np.errstate(over="ignore"):     # deadlines may overflow to infinity
+        e = np.minimum(wl.t1[:, None] + wl.t2[None, :], wmax)
     t1 = np.minimum(wl.t1, wmax)
     # past the longest wait no request pays a host term: exact zeros, not differences
     host = (a2[:, None, None] * (e + t1[:, None])[None] + pr.b2 + pr.b3) * (wl.t1 < wmax)[None, :, None]
     per = pr.a1 * t1[None, :, None] + host
     # a few roundings to multiples of the smallest denormal, where the costs are that small
-    return (2.0 * 64.0 * H.EPS * per * float(wl.ctx_tokens.astype(np.float64).sum()) / wl.n
+    return (2.0 * 80.0 * H.EPS * per * float(wl.ctx_tokens.astype(np.float64).sum()) / wl.n
             + 4 * 5e-324)
 
 
@@ -63,7 +66,8 @@ def _check(kvr, oracle_mod, wl):
 # 4,095 (one range) and 4,096 (fused prefix), two and more ranges; K1 > K2; K2 = 1
 @pytest.mark.parametrize("k1,k2", [(1, 1), (1, 298), (1, 299), (1, 300), (1, 1834), (1, 1835),
                                    (1, 1836), (1, 3881), (1, 3882), (1, 3883), (1, 3884),
-                                   (8, 1023), (64, 130), (130, 64), (300, 1), (16, 1024)])
+                                   (8, 1023), (64, 130), (130, 64), (300, 1), (16, 1024),
+                                   (16384, 1)])
 def test_threshold_counts(kvr, oracle_mod, k1, k2):
     _check(kvr, oracle_mod, workloads.random_case(700 + k1 + k2, 2500, k1, k2, 3, ties=True,
                                                      inf_last=k2 > 1))

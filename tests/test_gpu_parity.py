@@ -193,15 +193,21 @@ def test_max_size_2p24_waits(kvr, oracle_mod):
                                                            g.last_inf)[0]), rb)
 
 
-@pytest.mark.parametrize("n", [(1 << 22) - 1, (1 << 22) + 1001, (1 << 23) + 4095],
-                         ids=["2p22-1-keys", "2p22+1001-kpt8", "2p23+4095-kpt16"])
-def test_sorted_digit_byte_passes(kvr, oracle_mod, n):
-    """From 2^22 waits each digit pass counts the digit bytes that the
-    previous scatter wrote instead of reading the keys (one below that, the
-    keys): ragged samples at 8 and 16 keys per thread, with duplicated waits
-    and both signed zeros; the stable order bit for bit, and the costs with
-    and without a requested order against the oracle's closed form."""
-    wl = workloads.random_case(300 + n % 97, n, 2, 40, 4, ties=True)
+@pytest.mark.parametrize("n,k1,k2", [((1 << 20) + 1, 3, 172), ((1 << 22) - 1, 2, 1025),
+                                     ((1 << 22) + 1001, 2, 1026), ((1 << 23) + 4095, 4, 1026),
+                                     ((1 << 24) + 5, 82, 101)],
+                         ids=["2p20+1-own-scan", "2p22-1-keys", "2p22+1001-kpt8",
+                              "2p23+4095-kpt16", "2p24+5-scan-runs"])
+def test_sorted_scans_of_large_samples(kvr, oracle_mod, n, k1, k2):
+    """Beyond 2^20 waits a requested order with more than n / 2,048 policies takes the
+    costs from the sort too: tile scans of their own; from 2^22 waits each digit pass
+    counts the digit bytes that the previous scatter wrote (over the space of the prefix
+    sums) instead of reading the keys; from 2^23 tiles of 4,096 keys; beyond 2^24 the
+    scan of the tile sums takes runs of more than eight.  Ragged samples with duplicated
+    waits and both signed zeros: the stable order bit for bit, and the costs against the
+    oracle's closed form; without an order the same costs from the bins."""
+    assert k1 * k2 > n // 2048 and k1 * k2 <= 16384
+    wl = workloads.random_case(300 + n % 97, n, k1, k2, 2, ties=True)
     rng = np.random.default_rng(n)
     wl.wait_s[rng.integers(0, n, n // 64)] = -0.0   # sorts as +0.0, in input order
     pr = oracle_mod.workload_prices(wl)
@@ -214,6 +220,20 @@ def test_sorted_digit_byte_passes(kvr, oracle_mod, n):
     cost = kvr.kvr_cost_grid(_dev(wl.wait_s, _f64()), _dev(wl.ctx_tokens, _i32()),
                              _lib_prices(kvr, wl), g, method=kvr.KVR_SORTED)
     assert_costs(_np(cost), closed)
+
+
+@pytest.mark.parametrize("n", [2049, (1 << 20) + 1, (1 << 22) + 1001])
+def test_sorted_beyond_the_bins(kvr, oracle_mod, n):
+    """More than 16,384 policies without an order: the context sizes ride through the
+    sort as its payload, the scans read them in sorted order, and a thread per policy
+    searches the waits; against the oracle's closed form."""
+    wl = workloads.random_case(320 + n % 97, n, 5, 3280, 1, ties=True)
+    pr = oracle_mod.workload_prices(wl)
+    g = kvr.PolicyGrid(wl.t1, wl.t2, wl.lam)
+    cost = kvr.kvr_cost_grid(_dev(wl.wait_s, _f64()), _dev(wl.ctx_tokens, _i32()),
+                             _lib_prices(kvr, wl), g, method=kvr.KVR_SORTED)
+    assert_costs(_np(cost), oracle_mod.closed_form_grid(wl.wait_s, wl.ctx_tokens, pr, wl.t1, wl.t2,
+                                                        wl.lam))
 
 
 @pytest.mark.parametrize("case", [(201, 500, 2, 70, 5, 3, None), (202, 1300, 1, 65, 16, 4, 777),

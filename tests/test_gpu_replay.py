@@ -119,12 +119,10 @@ def test_replay_many_timers_in_chunks(kvr, oracle_mod):
 
 
 @pytest.mark.parametrize("reps,n,n_timers", [(4096, 2500, 9), (4096, 5000, 5)])
-def test_replay_forty_lane_waves(kvr, oracle_mod, reps, n, n_timers):
-    """Batches whose (timer, sequence) lanes would need a second round of
-    64-lane waves (LDS holds two per CU) run as 40-lane waves, four per CU:
-    36,864 lanes with up to 4,096 requests per sequence, 20,480 with up to
-    8,192.  Sampled rows against the oracle, every row's admissions within
-    their bounds."""
+def test_replay_large_batches(kvr, oracle_mod, reps, n, n_timers):
+    """Batches of more (timer, sequence) pairs than the card holds waves for, with
+    rows of up to 4,096 and up to 8,192 requests.  Sampled rows against the oracle,
+    every row's admissions within their bounds."""
     rc = workloads.replay_case("lognormal", 2 * LC, reps=reps, n=n, seed=123)
     t2 = np.concatenate([np.geomspace(60.0, 20000.0, n_timers - 1), [np.inf]])
     cost, rest, adm = _run(kvr, rc.arrival_s, rc.wait_s, t2, 425)
@@ -170,3 +168,19 @@ def test_replay_odd_rows(kvr, oracle_mod, shape, n):
     T = rng.integers(1, 50, (2, n)).astype(np.int32)
     for c2 in (1, 5, 64, n + 7):
         _check(kvr, oracle_mod, arr, w, [2.0, 33.0, 5.0e307, math.inf], c2, T)
+
+
+@pytest.mark.parametrize("c2", [1, 2])
+def test_replay_more_rows_than_blocks(kvr, oracle_mod, c2):
+    """More rows, and more (timer, row) pairs, than the 2^20 blocks of a launch: blocks
+    take further ones and start them from clean tables.  Short rows of whole instants
+    with many ties, against the oracle, every row."""
+    reps, n, rng = (1 << 20) + 4099, 5, np.random.Generator(np.random.PCG64(77))
+    arr = np.cumsum(rng.integers(0, 3, (reps, n)), axis=1).astype(np.float64)
+    w = rng.integers(0, 6, (reps, n)).astype(np.float64)
+    t2 = np.array([2.0, np.inf])
+    cost, rest, adm = _run(kvr, arr, w, t2, c2)
+    oc, orr = oracle_mod.capacity_replay_batch(arr, w, c2, t2, 0.02, 1.91)
+    assert np.array_equal(rest, orr)
+    assert np.all(np.abs(cost - oc) <= 4 * np.spacing(oc))
+    assert np.all((adm >= 1) & (adm <= n) & (rest <= adm))

@@ -34,19 +34,21 @@ def test_order_is_stable(n, law):
 
 
 @pytest.mark.parametrize("n,k2", [(1048575, 3), (1048576, 512), (1048576, 513), (1048576, 2)])
-def test_costs_beside_the_order(n, k2):
+def test_costs_beside_the_order(oracle_mod, n, k2):
     """From 2^20 waits and up to n / 2,048 policies the costs beside a requested
-    order come from the per-bin sums: within rounding (sums of n products of one
-    sign, 1e-12 relative) of those without the order, on both sides of the line."""
+    order come from the per-bin sums, on the other side of the line from the scans of the
+    sorted waits: against the oracle's closed form on both, which like them sums n
+    products of one sign (1e-12 relative), with the order bit for bit."""
     import torch
     import paper_2608_30830_amd as kvr
     rng = np.random.Generator(np.random.PCG64(n + k2))
-    w = torch.as_tensor(rng.exponential(1800.0, n)).cuda()
-    T = torch.as_tensor(rng.integers(1, 40000, n, dtype=np.int32)).cuda()
+    w, T = rng.exponential(1800.0, n), rng.integers(1, 40000, n, dtype=np.int32)
     p = kvr.kvr_prices_from_platform(131072.0, 250e9, 50e9, 2e4)
-    g = kvr.PolicyGrid([0.0], list(np.geomspace(5.0, 90000.0, k2 - 1)) + [np.inf], [0.2, 0.9])
-    cost, perm = kvr.kvr_cost_grid(w, T, p, g, method=kvr.KVR_SORTED, want_perm=True)
-    ref = kvr.kvr_cost_grid(w, T, p, g, method=kvr.KVR_SORTED)
-    cost, ref = cost.cpu().numpy(), ref.cpu().numpy()
-    assert np.all(np.abs(cost - ref) <= 1e-12 * np.abs(ref))
-    assert np.array_equal(perm.cpu().numpy(), np.argsort(w.cpu().numpy(), kind="stable"))
+    t2, lam = np.append(np.geomspace(5.0, 90000.0, k2 - 1), np.inf), np.array([0.2, 0.9])
+    g = kvr.PolicyGrid([0.0], t2, lam)
+    cost, perm = kvr.kvr_cost_grid(torch.as_tensor(w).cuda(), torch.as_tensor(T).cuda(), p, g,
+                                   method=kvr.KVR_SORTED, want_perm=True)
+    ref = oracle_mod.closed_form_grid(w, T, oracle_mod.prices_from_platform(131072.0, 250e9, 50e9, 2e4),
+                                      np.zeros(1), t2, lam)
+    assert np.all(np.abs(cost.cpu().numpy() - ref) <= 1e-12 * np.abs(ref))
+    assert np.array_equal(perm.cpu().numpy(), np.argsort(w, kind="stable"))

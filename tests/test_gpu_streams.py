@@ -68,10 +68,10 @@ def case(kvr):
                 grid=kvr.PolicyGrid(wl.t1, wl.t2, wl.lam))
 
 
-@pytest.mark.parametrize("method", ["brute", "sorted"])
+@pytest.mark.parametrize("method", ["brute", "sorted", "order"])
 def test_cost_grid_side_stream(kvr, case, method):
     m = kvr.KVR_BRUTE if method == "brute" else kvr.KVR_SORTED
-    perm = method == "sorted"
+    perm = method == "order"
     ref = kvr.kvr_cost_grid(case["w"], case["T"], case["prices"], case["grid"], m, want_perm=perm)
     got = _side(lambda s: kvr.kvr_cost_grid(case["w"], case["T"], case["prices"], case["grid"], m,
                                             want_perm=perm, stream=s, check=False))

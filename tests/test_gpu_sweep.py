@@ -72,13 +72,14 @@ def test_grid_shapes(kvr, oracle_mod, case):
             assert_costs(_np(bc)[r], rbc)
 
 
-@pytest.mark.parametrize("n", [2047, 2048, 2049, 4096, 4097, 262143, 262144, 300001, 524288])
+@pytest.mark.parametrize("n", [2047, 2048, 2049, 4096, 4097, 65536, 65537, 262143, 262144, 262145,
+                               300001, 524288, 524289])
 def test_sort_path_boundaries(kvr, oracle_mod, n):
     """Sample sizes around the one-block sort (at most 2,048 waits), around the
-    tile sizes of the multi-block sort (512-key tiles below 2^18 waits, 1,024
-    below 2^19, 2,048 from there) and a ragged last tile: the SORTED grid and
-    its order against the oracle, and the factored bootstrap, which sorts the
-    same way."""
+    tile sizes of the multi-block sort (512 keys up to 2^16 waits, 1,024 up to
+    2^18, 2,048 up to 2^19, 4,096 from there to 2^20) and ragged last tiles: the
+    SORTED grid and its order against the oracle, and the factored bootstrap,
+    which sorts the same way."""
     wl = workloads.random_case(7000 + n, n, 2, 70, 5, resamples=2, m=n, ties=True)
     pr = oracle_mod.workload_prices(wl)
     lp = _lib_prices(kvr, wl)
