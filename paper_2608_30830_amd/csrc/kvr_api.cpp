@@ -606,7 +606,7 @@ int kvr_bootstrap_factored(const double *d_wait_s, const int32_t *d_ctx_tokens, 
     const size_t off_cpos = take(small ? sizeof(uint32_t) * n : 0);
     const size_t off_u1 = take(sizeof(int32_t) * g->n_t1);
     const size_t off_ue = take(sizeof(int32_t) * P);
-    const size_t off_qslot = take(sizeof(int32_t) * (n + 1));
+    const size_t off_qslot = take(small ? 0 : sizeof(int32_t) * (n + 1));
     const size_t off_qbits = take(sizeof(uint32_t) * ((n + 32) / 32));
     const size_t off_qbase = take(sizeof(int32_t) * ((n + 32) / 32));
     const size_t off_TQ = take(sizeof(double) * 2 * Rb * nqs);
@@ -632,7 +632,7 @@ int kvr_bootstrap_factored(const double *d_wait_s, const int32_t *d_ctx_tokens, 
     fw.cpos = small ? at<uint32_t>(d_ws, off_cpos) : nullptr;
     fw.u1 = at<int32_t>(d_ws, off_u1);
     fw.ue = at<int32_t>(d_ws, off_ue);
-    fw.qslot = at<int32_t>(d_ws, off_qslot);
+    fw.qslot = small ? nullptr : at<int32_t>(d_ws, off_qslot);
     fw.qbits = at<uint32_t>(d_ws, off_qbits);
     fw.qbase = at<int32_t>(d_ws, off_qbase);
     fw.nqs = nqs;
@@ -757,8 +757,7 @@ int kvr_crossover_statistic(const double *d_wait_s, int64_t n, const kvr_prices 
     int *status = static_cast<int *>(d_ws);
     void *cnt = at<char>(d_ws, kStatusBytes);
     KVR_TRY(kvr::launch_clear_status(status, s));
-    KVR_TRY(kvr::launch_short_count(d_wait_s, nullptr, n, p->b3_per_token / p->a1_per_token, cnt,
-                                    status, s));
+    KVR_TRY(kvr::launch_short_count(d_wait_s, n, p->b3_per_token / p->a1_per_token, cnt, status, s));
     KVR_TRY(kvr::launch_fraction(cnt, n, d_count, d_fraction, s));
     return KVR_OK;
 }

@@ -15,7 +15,8 @@ struct FactoredWs {
                               // position, or nullptr (factored_small)
     int32_t *u1;              // [K1] sorted waits <= t1, then that position's query slot
     int32_t *ue;              // [K1*K2] sorted waits <= t1 + t2, then its query slot
-    int32_t *qslot;           // [n+1] query slot of each sorted position, -1 if none
+    int32_t *qslot;           // [n+1] query slot of each sorted position, -1 if none, or nullptr
+                              // (factored_small)
     uint32_t *qbits;          // [(n+32)/32] bit k: sorted position k is a query position
     int32_t *qbase;           // [(n+32)/32] query positions below each word of qbits
     int64_t nqs;              // query slots per row (an upper bound on the distinct positions)

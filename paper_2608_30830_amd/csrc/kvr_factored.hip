@@ -152,11 +152,11 @@ __device__ __forceinline__ int32_t slot_of(const uint32_t *__restrict__ qbits,
 }
 
 // Items 0..K1-1 and K1..K1+P-1: u1[a] and ue[f] from sorted positions to
-// slots; items K1+P .. K1+P+n: the slot of each sorted position 0..n, -1 if
-// it is no query position.
+// slots; items K1+P .. K1+P+last (for factored_prefix_kernel): the slot of each
+// sorted position 0..last, -1 if it is no query position.
 __global__ void __launch_bounds__(256) factored_remap_kernel(int32_t *__restrict__ u1,
                                                              int32_t *__restrict__ ue, int32_t K1,
-                                                             int64_t P, int64_t n,
+                                                             int64_t P, int64_t last,
                                                              const uint32_t *__restrict__ qbits,
                                                              const int32_t *__restrict__ qbase,
                                                              int32_t *__restrict__ qslot)
@@ -166,7 +166,7 @@ __global__ void __launch_bounds__(256) factored_remap_kernel(int32_t *__restrict
         u1[g] = slot_of(qbits, qbase, u1[g]);
     } else if (g - K1 < P) {
         ue[g - K1] = slot_of(qbits, qbase, ue[g - K1]);
-    } else if (g - K1 - P <= n) {
+    } else if (g - K1 - P <= last) {
         const int64_t k = g - K1 - P;
         qslot[k] = ((qbits[k >> 5] >> (k & 31)) & 1u) ? slot_of(qbits, qbase, k) : -1;
     }
@@ -997,8 +997,10 @@ hipError_t launch_factored(const SampleSrc &src, int64_t R, const Tables &tb, co
                        ws.ue, ws.qbits);
     hipLaunchKernelGGL(factored_slot_kernel, dim3(1), dim3(kFThreads), 0, stream, ws.qbits, ws.qbase,
                        nwords);
-    hipLaunchKernelGGL(factored_remap_kernel, dim3((unsigned)((tb.K1 + P + n + 1 + 255) / 256)),
-                       dim3(256), 0, stream, ws.u1, ws.ue, tb.K1, P, n, ws.qbits, ws.qbase,
+    // the small prefix kernel reads the slots from qbits and qbase itself
+    const int64_t last = ws.qslot != nullptr ? n : -1;
+    hipLaunchKernelGGL(factored_remap_kernel, dim3((unsigned)((tb.K1 + P + last + 1 + 255) / 256)),
+                       dim3(256), 0, stream, ws.u1, ws.ue, tb.K1, P, last, ws.qbits, ws.qbase,
                        ws.qslot);
     if ((err = hipGetLastError()) != hipSuccess) return err;
     // Groups of four host timers from where they fill a chunk on; fewer policies

@@ -143,11 +143,11 @@ hipError_t launch_replay(const double *arrival, const double *wait, const int32_
                          int64_t *admitted, double t_star, void *counts, int *status,
                          hipStream_t stream);
 
-// Controller tail: share of waits <= t_star and token total over N waits,
-// then the branch totals from the replay's per-row counts [reps][2].
+// Share of waits <= t_star among N (the crossover statistic), and the controller's
+// tail: the branch totals from the replay's per-row counts [reps][2].
 size_t count_ws_bytes();
-hipError_t launch_short_count(const double *wait, const int32_t *ctx, int64_t N, double t_star,
-                              void *count_ws, int *status, hipStream_t stream);
+hipError_t launch_short_count(const double *wait, int64_t N, double t_star, void *count_ws,
+                              int *status, hipStream_t stream);
 hipError_t launch_fraction(const void *count_ws, int64_t N, int64_t *count, double *fraction,
                            hipStream_t stream);
 hipError_t launch_controller_final(const int64_t *restored, const int64_t *admitted,

@@ -54,7 +54,12 @@ static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // fit LDS).  At 2^17 512 threads measured 88 against 96 for 256, at 200,000 95 against
 // 97 for 1,024.  Counting the next digit in the scatter (an atomic per key into its
 // destination's tile) in place of the histogram launches: 66 us at 5,003 waits but
-// 92 at 65,536 and 168 at 2^18.  Longer tiles give each
+// 92 at 65,536 and 168 at 2^18.
+//
+// Beyond 2^20 keys there are blocks enough either way, and longer tiles give each digit
+// longer runs of consecutive destinations: at 2^24 keys a scatter writes exactly its 24
+// bytes per key from 4,096-key tiles (103 us) and 12-37 % more from 2,048 (129-134 us); at
+// 2^22 the shorter tiles, twice as many, still win (23.4 against 29.4 us).
 constexpr int64_t kFoldTo = int64_t(1) << 20;
 constexpr int kFoldTiles = 256;
 
@@ -233,10 +238,7 @@ template <int KPT>
 __global__ void __launch_bounds__(kSortThreads) sort_hist_bytes_kernel(
     const uint8_t *__restrict__ dig, int64_t n, uint32_t *__restrict__ hist, int nblocks)
 {
-    using Vec = typename std::conditional<
-        KPT == 16, uint4,
-        typename std::conditional<KPT == 8, uint2,
-                                  typename std::conditional<KPT == 4, uint32_t, uint16_t>::type>::type>::type;
+    using Vec = typename std::conditional<KPT == 16, uint4, uint2>::type;
     static_assert(sizeof(Vec) == KPT, "one load of KPT bytes");
     __shared__ uint32_t h[256];
     h[threadIdx.x] = 0;
@@ -1001,12 +1003,13 @@ static hipError_t launch_closed_form(const uint64_t *skeys, const SortWs &ws, in
     return hipGetLastError();
 }
 
+// Keys from which the histograms read digit bytes (launch_digit_passes).
+constexpr int64_t kDigitBytesFrom = int64_t(1) << 22;
+
 // Unused dynamic LDS that holds the 4,096-key scatter at two blocks per CU
 // from 2^24 keys: three blocks per CU (52 KiB each) measured faster at 2^23
 // (0.585 against 0.634 ms per call on MI355X) but slower at 2^24 (1.287
 // against 1.256 ms, the same box).
-constexpr int64_t kDigitBytesFrom = int64_t(1) << 22;
-
 static size_t scatter_lds_pad(int kpt, int64_t n)
 {
     return (kpt == 16 && n >= (int64_t(1) << 24)) ? 4096 : 0;
