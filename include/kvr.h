@@ -372,7 +372,7 @@ int kvr_cost_grid_noalloc(const double *d_wait_s, const int32_t *d_ctx_tokens, i
  * (kvr_cost_grid and kvr_cost_grid_noalloc with KVR_BRUTE, kvr_bootstrap), the
  * whole sorted path from its first kernel (KVR_SORTED), the whole factored
  * path (kvr_bootstrap_factored), the replay
- * (kvr_capacity_replay), or the replay, count and final kernels
+ * (kvr_capacity_replay), or the replay, which also counts, and the final kernel
  * (kvr_controller_select).  kvr_set_profile_events(NULL, NULL)
  * stops it.  These two handles, kept per host thread, are the only state the
  * library holds between calls; the events stay owned by the caller.
