@@ -57,10 +57,17 @@ __global__ void stage_kernel(StagePlan sp, UploadPayload p)
         for (int i = threadIdx.x; i < sp.nzero; i += blockDim.x) sp.zero[i] = 0u;
     }
     for (int i = threadIdx.x; i < sp.n; i += blockDim.x) {
-        int64_t g = sp.from + i;
-        int t = 0;
-        while (t < 2 && g >= sp.cnt[t]) g -= sp.cnt[t++];
-        sp.dst[t][g] = p.v[i];
+        int64_t g = sp.from + i;   // by selects: an indexed sp.dst[t] is a load more per call
+        double *d = sp.dst[0];
+        if (g >= sp.cnt[0]) {
+            g -= sp.cnt[0];
+            d = sp.dst[1];
+            if (g >= sp.cnt[1]) {
+                g -= sp.cnt[1];
+                d = sp.dst[2];
+            }
+        }
+        d[g] = p.v[i];
     }
 }
 
