@@ -36,11 +36,12 @@ constexpr int64_t kR3ItemsPerLine = 1 << 14;
 // Blocks of the item searches, four to a CU; beyond them (LOOP) they loop over the
 // items.  Blocks that start as others end leave the CUs filled unevenly for the grid
 // kernel, which counts on about four waves per SIMD: 220,521 waits, 143 x 16 policies and
-// 12 loads 463 us per call with a block for every 32 items, 392 with these.  Long searches
-// of many items want more waves than that: 2^24 waits and 40 x 40 policies 8.94 ms against
-// 9.35, 2^22 and 8 x 33 817 us against 834; with few rows 2^24 and 1 x 65 1,147 against 1,120.
+// 12 loads 463 us per call with a block for every 32 items, 392 with these.  Many long
+// chains of searches want more waves than that: 196,608 waits and 64 x 256 policies 59 us
+// against 68 (the kernel alone), 2^22 and 8 x 33 817 against 834 (the call), 2^24 and 40 x 40
+// 8.94 ms against 9.35; with few rows 2^24 and 1 x 65 1,147 against 1,120 us.
 constexpr int64_t kR3BinsBlocks = 1024;
-constexpr int64_t kR3LoopItems = 1 << 20;
+constexpr int64_t kR3LoopSearches = 1 << 23;   // items x lines
 
 // Number of grid deadlines fl(t1[a] + t2[k]) strictly below x, from timer
 // tables t1[K1] and t2[K2] (in LDS when they fit there), along the rows (or
@@ -288,7 +289,7 @@ hipError_t launch_r3(const SampleSrc &src, int64_t R, const Tables &tb, const R3
     // 16 lines and 250,000 64.3 and 55.9; 64 lines and 250,000 144 and 106.
     const bool one = lines < 4 || items > kR3ManyItems || items > kR3ItemsPerLine * lines;
     const int64_t blocks = (items * (one ? 1 : 8) + 255) / 256;
-    const bool loop = blocks > kR3BinsBlocks && (lines < 8 || items <= kR3LoopItems);
+    const bool loop = blocks > kR3BinsBlocks && (lines < 8 || items * lines <= kR3LoopSearches);
     auto bins = one ? (loop ? r3_bins_kernel<1, true> : r3_bins_kernel<1, false>)
                     : (loop ? r3_bins_kernel<8, true> : r3_bins_kernel<8, false>);
     hipLaunchKernelGGL(bins, dim3((unsigned)(loop ? kR3BinsBlocks : blocks)), dim3(256), 0, stream,

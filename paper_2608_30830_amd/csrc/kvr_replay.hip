@@ -21,8 +21,8 @@
 // free.  replay_admit_kernel walks that recurrence 64 arrivals at a time, one
 // wave per (timer, sequence).
 //
-// Measured on MI355X, 8,192 sequences x 4,000 requests x 5 timers: 0.32 ms
-// for the releases and 0.38 ms for the walk, 0.66 ms per call.  The first form of this replay
+// Measured on MI355X, 8,192 sequences x 4,000 requests x 5 timers: 0.65 ms per call, traced
+// 0.31 ms for the releases and 0.37 ms for the walk.  The first form of this replay
 // (a bitonic sort of the resume instants, 1.08 ms, two binary searches per
 // request and timer, 0.36 ms, and one lane per (timer, sequence) stepping
 // through every arrival, 0.95 ms) took 2.31 ms per call; with 100 sequences x

@@ -324,12 +324,12 @@ def test_deadline_bin_searches(kvr, oracle_mod, k1, k2, over):
 
 
 @pytest.mark.parametrize("n,k1,k2", [(32768 - 81, 9, 9), (32768 - 80, 9, 9), (262144 - 9, 3, 3),
-                                     (262145 - 9, 3, 3), ((1 << 20) - 81, 9, 9),
-                                     ((1 << 20) - 80, 9, 9)])
+                                     (262145 - 9, 3, 3), (932067 - 81, 9, 9),
+                                     (932068 - 81, 9, 9)])
 def test_deadline_bin_loops(kvr, oracle_mod, n, k1, k2):
     """Around the sizes at which the search's blocks begin to loop over the items (1,024
-    blocks of 32 or 256) and, with eight rows or more, stop to (2^20 items): costs of one
-    sample against the oracle's closed form."""
+    blocks of 32 or 256) and, with eight rows or more, stop to (2^23 items times rows):
+    costs of one sample against the oracle's closed form."""
     wl = workloads.random_case(437, n, k1, k2, 3, ties=True)
     pr = oracle_mod.workload_prices(wl)
     g = kvr.PolicyGrid(wl.t1, wl.t2, wl.lam)
